@@ -247,6 +247,17 @@ void adi_seg_table_t(double Dd, double Ed, int K, T* tab) {
         tab[SEG_CQR + p] = (T)(ER / pv);
     }
     tab[SEG_E + 1] = (T)ER;
+    // reach of the reduced system's scans: a separator h blocks away enters
+    // with a factor of at most amax^h, amax = max E_R / pivot_p; from the
+    // distance on where amax^h / (1 - amax) is below 2^-60 (FP32: 2^-31) of
+    // the line's largest value, a seventh bit below its rounding, further
+    // scan steps only add what rounding drops
+    R amax = 0;
+    for (int p = 0; p < NR; ++p) amax = std::max(amax, std::fabs((R)tab[SEG_CQR + p]));
+    const R drop = std::ldexp((R)1, sizeof(T) == 8 ? -60 : -31);
+    int reach = 1;
+    for (R a = amax; reach < NR && !(a < drop * (1 - amax)); reach *= 2) a = a * a;
+    tab[SEG_E + 2] = (T)reach;
 }
 
 void adi_seg_table(double D, double E, int K, double* tab) { adi_seg_table_t<double>(D, E, K, tab); }
@@ -262,7 +273,7 @@ __device__ __forceinline__ T seg_rhs(const LineArgsT<T>& A, T cc, T own, T nb, T
 
 // Forward elimination of one block given its right-hand sides r[0..len)
 // (len <= kSegL); leaves the block's zero-end solution in r, returns its
-// last value in *last.
+// last value in *last.  Tb: the table's block part, in LDS.
 template <typename T>
 __device__ __forceinline__ void seg_block(const T* Tb, T E, int len, T (&r)[kSegL], T* last) {
     T z = 0;
@@ -288,22 +299,24 @@ __device__ __forceinline__ void seg_block(const T* Tb, T E, int len, T (&r)[kSeg
 // reaches every barrier).  The forward elimination z_p = (rho_p + E_R
 // z_{p-1}) / pivot_p and the back substitution x_p = z_p + (E_R / pivot_p)
 // x_{p+1} are first-order linear recurrences: each is evaluated as a
-// Hillis-Steele scan of affine maps in ceil(log2 NR) steps through two LDS
-// buffer pairs (a0, b0), (a1, b1) addressed by slot(p).  Returns x_p.
+// Hillis-Steele scan of affine maps through two LDS buffer pairs (a0, b0),
+// (a1, b1) addressed by slot(p).  The scan stops at the table's reach: the
+// line matrix is diagonally dominant, so E_R / pivot is tiny (7e-10 at
+// dx = dy) and one step, not log2 NR = 7 at 94 blocks, is all that FP64 can
+// see.  ip, cq: 1 / pivot_p and E_R / pivot_p.  Returns x_p.
 template <typename T, typename Slot>
-__device__ __forceinline__ T seg_scan(const T* Tb, int NR, int p, bool act, T rho, Slot slot, T* a0, T* b0,
-                                      T* a1, T* b1) {
+__device__ __forceinline__ T seg_scan(T ER, T ip, T cq, int reach, int NR, int p, bool act, T rho, Slot slot,
+                                      T* a0, T* b0, T* a1, T* b1) {
     T a = 0, b = 0;
     if (act) {
-        const T ip = Tb[SEG_IPIVR + p];
-        a = p > 0 ? Tb[SEG_E + 1] * ip : T(0);
+        a = p > 0 ? ER * ip : T(0);
         b = rho * ip;
         a0[slot(p)] = a;
         b0[slot(p)] = b;
     }
     __syncthreads();
     T *ra = a0, *rb = b0, *wa = a1, *wb = b1;
-    for (int h = 1; h < NR; h <<= 1) {
+    for (int h = 1; h < reach; h <<= 1) {
         if (act) {
             if (p >= h) {
                 const int q = slot(p - h);
@@ -317,37 +330,65 @@ __device__ __forceinline__ T seg_scan(const T* Tb, int NR, int p, bool act, T rh
         T* t = ra; ra = wa; wa = t;
         t = rb; rb = wb; wb = t;
     }
-    // b = z_p; now x_p = c_p x_{p+1} + z_p, scanned from the end
-    T c = (act && p < NR - 1) ? Tb[SEG_CQR + p] : T(0);
+    // b = z_p; now x_p = c_p x_{p+1} + z_p, scanned from the end (the
+    // buffers last read may still be in use: write the other pair)
+    T c = (act && p < NR - 1) ? cq : T(0);
     if (act) {
-        ra[slot(p)] = c;
-        rb[slot(p)] = b;
+        wa[slot(p)] = c;
+        wb[slot(p)] = b;
     }
     __syncthreads();
-    for (int h = 1; h < NR; h <<= 1) {
+    { T* t = ra; ra = wa; wa = t; t = rb; rb = wb; wb = t; }
+    for (int h = 1; h < reach; h <<= 1) {
         if (act) {
             if (p + h < NR) {
                 const int q = slot(p + h);
                 b = fma(c, rb[q], b);
                 c = c * ra[q];
             }
-            wa[slot(p)] = c;
-            wb[slot(p)] = b;
+            if (2 * h < reach) {
+                wa[slot(p)] = c;
+                wb[slot(p)] = b;
+            }
         }
-        __syncthreads();
+        if (2 * h < reach) __syncthreads();
         T* t = ra; ra = wa; wa = t;
         t = rb; rb = wb; wb = t;
     }
     return b;
 }
 
+// The table's block part (SEG_IPIV .. SEG_GL), copied to LDS while the
+// field's loads are in flight: the elimination then waits for no scalar load.
+constexpr int kSegHead = 4 * kSegL;
+template <typename T>
+__device__ __forceinline__ void seg_stage_table(const T* Tb, T* tab) {
+    if (threadIdx.x < kSegHead) tab[threadIdx.x] = Tb[threadIdx.x];
+}
+
+// Two consecutive values of a row (aligned to one value only).
+template <typename T> struct SegPair;
+template <> struct SegPair<double> { typedef double type __attribute__((ext_vector_type(2), aligned(8))); };
+template <> struct SegPair<float> { typedef float type __attribute__((ext_vector_type(2), aligned(4))); };
+
+// Whether the solve is over; read behind the issued loads (in place, only
+// the stores at the end depend on it), so its latency is not waited for first.
+__device__ __forceinline__ bool seg_done(const Ctrl* ctrl) {
+    asm volatile("" ::: "memory");   // the loads above stay above
+    return ctrl != nullptr && ctrl->done;
+}
+
 // Row lines of the parity in A, tile `tile` (W = NT / S lines), one
-// workgroup of NT threads.  The lines' right-hand sides are staged in
-// LDS row by row (coalesced); thread (line c, block s), s fastest, solves its
-// block from LDS; the solution goes back through LDS and is written row by
-// row with the relaxation.  lds: W * S * kSegBS values.
+// workgroup of NT threads.  The lines are read in pairs of unknowns (coalesced,
+// 16 bytes a lane in FP64), eight pairs a thread, their right-hand sides
+// staged in LDS and their old values kept in registers; thread (line c, block
+// s), s fastest, solves its block from LDS; the solution goes back through
+// LDS and is written in the same pairs with the relaxation.  Bound by
+// latency: one round trip for all of a thread's loads, then the block's
+// serial elimination.  lds: NT * kSegBS + kSegHead values.
 template <typename T, int NT>
-static __device__ void adi_rows_seg(const LineArgsT<T>& A, int tile, T* lds) {
+static __device__ void adi_rows_seg(const LineArgsT<T>& A, const Ctrl* ctrl, int tile, T* lds) {
+    typedef typename SegPair<T>::type T2;
     const int K = A.m - 2;
     const int S = seg_count(K);
     const int W = NT / S;
@@ -357,44 +398,78 @@ static __device__ void adi_rows_seg(const LineArgsT<T>& A, int tile, T* lds) {
     const int nl = min(W, nlines - line0);
     if (nl <= 0) return;
     const size_t P = (size_t)A.P;
-    const T* Tb = A.seg;
-    const T E = Tb[SEG_E];
+    const T* Tg = A.seg;
+    T* Tb = lds + NT * kSegBS;
     const T cc = (T)A.cy;
     const int LW = S * kSegBS;
     const int tid = threadIdx.x;
-    const int total = nl * K;
-    // element q of the tile is (line q / K, unknown q % K)
-    const float invK = 1.0f / (float)K;
-    constexpr int kU = 8;   // elements in flight per thread
-    for (int q0 = tid; q0 < total; q0 += kU * NT) {
-        T r[kU];
-        int slot[kU];
-#pragma unroll
-        for (int v = 0; v < kU; ++v) {
-            const int q = q0 + v * NT;
-            slot[v] = -1;
-            r[v] = 0;
-            if (q < total) {
-                const int c = seg_div(q, invK);
-                const int k = q - c * K;
-                const size_t row = (size_t)(first + 2 * (line0 + c)) * P;
-                const size_t o = row + k + 1;
-                // the line's own old value enters only with relaxation inside
-                const T own = A.form == 0 ? T(0) : A.u[o];
-                r[v] = seg_rhs<T>(A, cc, own, A.u[o - P] + A.u[o + P], A.f != nullptr ? A.f[o] : T(0));
-                if (k == 0) r[v] = r[v] + E * A.u[row];
-                if (k == K - 1) r[v] = r[v] + E * A.u[row + A.m - 1];
-                slot[v] = c * LW + (k >> 4) * kSegBS + (k & 15);
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < kU; ++v)
-            if (slot[v] >= 0) lds[slot[v]] = r[v];
-    }
-    __syncthreads();
+    // pair q of the tile: unknowns k, k + 1 (k = 2 (q % NP)) of line q / NP;
+    // K < 16 S, so W lines have at most 8 NT pairs
+    const int NP = (K + 1) >> 1;
+    const int total = nl * NP;
+    const float invN = 1.0f / (float)NP;
+    constexpr int kU = 8, kG = sizeof(T) == 8 ? 4 : 8;   // pairs per thread; in flight at once
+    T2 own[kU];
     const int c = seg_div(tid, 1.0f / (float)S);
     const int s = tid - c * S;
     const bool act = c < nl;
+    const bool sep = act && s < S - 1;
+    const T E = Tg[SEG_E];
+    T ip = 0, cq = 0;
+    const T ER = Tg[SEG_E + 1];
+    const int reach = __builtin_amdgcn_readfirstlane((int)Tg[SEG_E + 2]);
+    if (sep) {
+        ip = Tg[SEG_IPIVR + s];
+        cq = Tg[SEG_CQR + s];
+    }
+    seg_stage_table<T>(Tg, Tb);
+#pragma unroll
+    for (int g = 0; g < kU; g += kG) {
+        T2 up[kG], dn[kG], fv[kG];
+        T end[kG];
+        int slot[kG];
+        bool two[kG];
+#pragma unroll
+        for (int v = 0; v < kG; ++v) {
+            const int q = tid + (g + v) * NT;
+            slot[v] = -1;
+            two[v] = false;
+            up[v] = dn[v] = fv[v] = own[g + v] = T2{0, 0};
+            end[v] = 0;
+            if (q < total) {
+                const int l = seg_div(q, invN);
+                const int k = 2 * (q - l * NP);
+                const size_t row = (size_t)(first + 2 * (line0 + l)) * P;
+                const size_t o = row + k + 1;      // k + 1 <= K: the pair ends at node m - 1 at most
+                own[g + v] = *reinterpret_cast<const T2*>(A.u + o);
+                up[v] = *reinterpret_cast<const T2*>(A.u + o - P);
+                dn[v] = *reinterpret_cast<const T2*>(A.u + o + P);
+                if (A.f != nullptr) fv[v] = *reinterpret_cast<const T2*>(A.f + o);
+                if (k == 0) end[v] = A.u[row];
+                if (k + 2 == K) end[v] = A.u[row + A.m - 1];
+                slot[v] = l * LW + (k >> 4) * kSegBS + (k & 15);
+                two[v] = k + 1 < K;
+                // K = 1 or 2: a pair holding both ends (its left end is added below)
+            }
+        }
+        if (g == 0 && seg_done(ctrl)) return;      // uniform over the workgroup
+#pragma unroll
+        for (int v = 0; v < kG; ++v) {
+            if (slot[v] < 0) continue;
+            const int q = tid + (g + v) * NT;
+            const int l = seg_div(q, invN);
+            const int k = 2 * (q - l * NP);
+            const T2 o2 = own[g + v];
+            T r0 = seg_rhs<T>(A, cc, o2.x, up[v].x + dn[v].x, fv[v].x);
+            T r1 = seg_rhs<T>(A, cc, o2.y, up[v].y + dn[v].y, fv[v].y);
+            if (k == 0) r0 = r0 + E * (k + 2 == K ? A.u[(size_t)(first + 2 * (line0 + l)) * P] : end[v]);
+            if (k + 1 == K) r0 = r0 + E * o2.y;                 // the line's last unknown; o2.y is its end value
+            if (k + 2 == K) r1 = r1 + E * end[v];
+            lds[slot[v]] = r0;
+            if (two[v]) lds[slot[v] + 1] = r1;
+        }
+    }
+    __syncthreads();
     const int len = s < S - 1 ? kSegL : K - (S - 1) * (kSegL + 1);
     T* blk = lds + c * LW + s * kSegBS;
     T y[kSegL];
@@ -409,11 +484,10 @@ static __device__ void adi_rows_seg(const LineArgsT<T>& A, int tile, T* lds) {
     __syncthreads();
     if (S > 1) {
         // slots 2..5 of each block are free now (its unknowns live in y)
-        const bool sep = act && s < S - 1;
         const T rho = sep ? fma(E, blk[1] + blk[kSegBS], blk[kSegL]) : T(0);
         T* lb = lds + c * LW;
-        const auto slot = [](int p) { return p * kSegBS; };
-        const T x = seg_scan<T>(Tb, S - 1, s, sep, rho, slot, lb + 2, lb + 3, lb + 4, lb + 5);
+        const auto at = [](int p) { return p * kSegBS; };
+        const T x = seg_scan<T>(ER, ip, cq, reach, S - 1, s, sep, rho, at, lb + 2, lb + 3, lb + 4, lb + 5);
         if (sep) blk[kSegL + 1] = x;
         __syncthreads();
     }
@@ -433,105 +507,122 @@ static __device__ void adi_rows_seg(const LineArgsT<T>& A, int tile, T* lds) {
     }
     __syncthreads();
     const T w = (T)A.omega;
-    for (int q0 = tid; q0 < total; q0 += kU * NT) {
-        T old[kU], t[kU];
-        size_t at[kU];
 #pragma unroll
-        for (int v = 0; v < kU; ++v) {
-            const int q = q0 + v * NT;
-            at[v] = 0;
-            old[v] = t[v] = 0;
-            if (q < total) {
-                const int c2 = seg_div(q, invK);
-                const int k = q - c2 * K;
-                at[v] = (size_t)(first + 2 * (line0 + c2)) * P + k + 1;
-                t[v] = lds[c2 * LW + (k >> 4) * kSegBS + (k & 15)];
-                if (A.form == 0) old[v] = A.u[at[v]];
-            }
+    for (int v = 0; v < kU; ++v) {
+        const int q = tid + v * NT;
+        if (q >= total) continue;
+        const int l = seg_div(q, invN);
+        const int k = 2 * (q - l * NP);
+        T* at = A.u + (size_t)(first + 2 * (line0 + l)) * P + k + 1;
+        const int sl = l * LW + (k >> 4) * kSegBS + (k & 15);
+        T2 t{lds[sl], lds[sl + 1]};
+        if (A.form == 0) {
+            t.x = own[v].x + w * (t.x - own[v].x);
+            t.y = own[v].y + w * (t.y - own[v].y);
         }
-#pragma unroll
-        for (int v = 0; v < kU; ++v)
-            if (q0 + v * NT < total) A.u[at[v]] = (A.form == 0) ? old[v] + w * (t[v] - old[v]) : t[v];
+        if (k + 1 < K)
+            *reinterpret_cast<T2*>(at) = t;
+        else
+            *at = t.x;
     }
 }
 
-// Column lines of the parity in A, tile `tile` (W = NT / S lines), one
-// workgroup of NT threads; thread (line c, block s), c fastest,
-// so a wavefront's accesses to one row are contiguous.  Each thread keeps
-// its block's old values and solution in registers.  sh: 5 * NT values
-// (first and last block values, separator values, scan buffers).
+// Column lines of the parity in A, tile `tile` (W lines, seg_lines), one
+// workgroup of NT threads; thread (line c, block s), c fastest, so a
+// wavefront's accesses to one row are contiguous.  A node and one of its
+// neighbours across the line come in one aligned pair load, the other
+// neighbour from the next pair (the same cache line).  Each thread keeps its
+// block's old values and solution in registers.  sh: 5 * NT + kSegHead
+// values (first block values, then separator values; scan buffers).
 template <typename T, int NT>
-static __device__ void adi_cols_seg(const LineArgsT<T>& A, int tile, T* sh) {
+static __device__ void adi_cols_seg(const LineArgsT<T>& A, const Ctrl* ctrl, int tile, T* sh) {
+    typedef typename VecT<T, 2>::type T2;
     const int K = A.n - 2;
     const int S = seg_count(K);
-    const int W = NT / S;
+    const int W = seg_lines_of(1, K, NT);
     const int first = A.parity ? 1 : 2;
     const int nlines = A.m - 2 >= first ? (A.m - 2 - first) / 2 + 1 : 0;
     const int line0 = tile * W;
     const int nl = min(W, nlines - line0);
     if (nl <= 0) return;
     const size_t P = (size_t)A.P;
-    const T* Tb = A.seg;
-    const T E = Tb[SEG_E];
+    const T* Tg = A.seg;
+    T* Tb = sh + 5 * NT;
+    const T E = Tg[SEG_E], ER = Tg[SEG_E + 1];
+    const int reach = __builtin_amdgcn_readfirstlane((int)Tg[SEG_E + 2]);
     const T cc = (T)A.cx;
     const int tid = threadIdx.x;
-    const int s = seg_div(tid, 1.0f / (float)W);
+    const int s = tid >> (31 - __builtin_clz(W));      // W: a power of two
     const int c = tid - s * W;
     const bool act = c < nl && s < S;
+    const bool sep = act && s < S - 1;
     const int len = s < S - 1 ? kSegL : K - (S - 1) * (kSegL + 1);
     const int i = first + 2 * (line0 + c);
     const int k0 = s * (kSegL + 1);
+    const bool odd = (i & 1) != 0;                     // uniform over the launch
     T* yF = sh;
-    T* yE = sh + NT;
-    T* xs = sh + 2 * NT;
     const int me = s * W + c;
     T y[kSegL], old[kSegL];
-    T osep = 0, rsep = 0, e = 0;
+    T osep = 0, rsep = 0, e = 0, ip = 0, cq = 0;
+    seg_stage_table<T>(Tg, Tb);
+    if (sep) {
+        ip = Tg[SEG_IPIVR + s];
+        cq = Tg[SEG_CQR + s];
+    }
     if (act) {
-        const T* up = A.u + (size_t)(k0 + 1) * P + i;
+        const T* up = A.u + (size_t)(k0 + 1) * P + (i & ~1);   // the node's aligned pair
+        const int third = odd ? 2 : -1;
         const T* fp = A.f != nullptr ? A.f + (size_t)(k0 + 1) * P + i : nullptr;
+        T head = 0, tail = 0;
+        if (s == 0) head = A.u[i];
+        if (s == S - 1 || k0 + kSegL == K - 1) tail = A.u[(size_t)(A.n - 1) * P + i];
+        const auto node = [&](int k, T& own, T& r) {
+            const T2 q = *reinterpret_cast<const T2*>(up + (size_t)k * P);
+            const T t = up[(ptrdiff_t)((size_t)k * P) + third];
+            own = odd ? q.y : q.x;
+            // the same sum of the west and east neighbours
+            const T nb = odd ? q.x + t : t + q.y;
+            r = seg_rhs<T>(A, cc, own, nb, fp != nullptr ? fp[(size_t)k * P] : T(0));
+        };
 #pragma unroll
         for (int k = 0; k < kSegL; ++k) {
             old[k] = 0;
             y[k] = 0;
-            if (k < len) {
-                const T* q = up + (size_t)k * P;
-                old[k] = q[0];
-                y[k] = seg_rhs<T>(A, cc, q[0], q[-1] + q[1], fp != nullptr ? fp[(size_t)k * P] : T(0));
-            }
+            if (k < len) node(k, old[k], y[k]);
         }
-        if (s == 0) y[0] = y[0] + E * A.u[i];
+        if (s == 0) y[0] = y[0] + E * head;
         if (len > 0 && k0 + len == K) {
 #pragma unroll
             for (int k = 0; k < kSegL; ++k)
-                if (k == len - 1) y[k] = y[k] + E * A.u[(size_t)(A.n - 1) * P + i];
+                if (k == len - 1) y[k] = y[k] + E * tail;
         }
         if (s < S - 1) {
-            const T* q = up + (size_t)kSegL * P;
-            osep = q[0];
-            rsep = seg_rhs<T>(A, cc, q[0], q[-1] + q[1], fp != nullptr ? fp[(size_t)kSegL * P] : T(0));
-            if (k0 + kSegL == K - 1) rsep = rsep + E * A.u[(size_t)(A.n - 1) * P + i];
+            node(kSegL, osep, rsep);
+            if (k0 + kSegL == K - 1) rsep = rsep + E * tail;
         }
+    }
+    if (seg_done(ctrl)) return;                        // uniform over the workgroup
+    __syncthreads();                                   // the table is staged
+    if (act) {
         seg_block<T>(Tb, E, len, y, &e);
         yF[me] = len > 0 ? y[0] : T(0);
-        yE[me] = e;
     }
     __syncthreads();
     if (S > 1) {
-        const bool sep = act && s < S - 1;
         const T rho = sep ? fma(E, e + yF[me + W], rsep) : T(0);
-        const auto slot = [W, c](int p) { return p * W + c; };
-        const T x = seg_scan<T>(Tb, S - 1, s, sep, rho, slot, yE, xs, sh + 3 * NT, sh + 4 * NT);
-        // yF is read above until every thread has passed the scan's first barrier
-        if (sep) xs[me] = x;
+        const auto at = [W, c](int p) { return p * W + c; };
+        const T x = seg_scan<T>(ER, ip, cq, reach, S - 1, s, sep, rho, at, sh + NT, sh + 2 * NT, sh + 3 * NT,
+                                sh + 4 * NT);
+        // yF is free: every thread passed the scan's first barrier after reading it
+        if (sep) yF[me] = x;
         __syncthreads();
     }
     if (act) {
         const T w = (T)A.omega;
-        const T xl = s > 0 ? xs[me - W] : T(0);
+        const T xl = s > 0 ? yF[me - W] : T(0);
         T* up = A.u + (size_t)(k0 + 1) * P + i;
         if (s < S - 1) {
-            const T xr = xs[me];
+            const T xr = yF[me];
 #pragma unroll
             for (int k = 0; k < kSegL; ++k) {
                 const T t = fma(xr, Tb[SEG_G + kSegL - 1 - k], fma(xl, Tb[SEG_G + k], y[k]));
@@ -551,18 +642,16 @@ static __device__ void adi_cols_seg(const LineArgsT<T>& A, int tile, T* sh) {
 
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void k_adi_rows_seg(LineArgsT<T> A, int ntiles) {
-    if (A.ctrl != nullptr && A.ctrl->done) return;
-    __shared__ T lds[NT * kSegBS];
+    __shared__ T lds[NT * kSegBS + kSegHead];
     const int t = xcd_remap(blockIdx.x, gridDim.x);
-    if (t < ntiles) adi_rows_seg<T, NT>(A, t, lds);
+    if (t < ntiles) adi_rows_seg<T, NT>(A, A.ctrl, t, lds);
 }
 
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void k_adi_cols_seg(LineArgsT<T> A, int ntiles) {
-    if (A.ctrl != nullptr && A.ctrl->done) return;
-    __shared__ T sh[5 * NT];
+    __shared__ T sh[5 * NT + kSegHead];
     const int t = xcd_remap(blockIdx.x, gridDim.x);
-    if (t < ntiles) adi_cols_seg<T, NT>(A, t, sh);
+    if (t < ntiles) adi_cols_seg<T, NT>(A, A.ctrl, t, sh);
 }
 
 // ------------------------------------------------------- merged batch launches
@@ -614,23 +703,21 @@ __global__ __launch_bounds__(kBlock) void k_batch_adi_cols(const BatchItem* item
 // Segmented solver over all grids: tiles of seg_lines lines of one grid,
 // dealt XCD-contiguously (neighbouring tiles share boundary lines).
 template <typename T, int NT>
-__global__ __launch_bounds__(NT) void k_batch_adi_rows_seg(const BatchItem* items, const int* tmap, int total) {
-    __shared__ T lds[NT * kSegBS];
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_batch_adi_rows_seg(const BatchItem* items, const int* tmap, int total) {
+    __shared__ T lds[NT * kSegBS + kSegHead];
     for (int t = xcd_remap(blockIdx.x, gridDim.x); t < total; t += gridDim.x) {
         const BatchItem& it = items[tmap[t]];
-        if (it.ctrl->done) continue;
-        adi_rows_seg<T, NT>(line_args<T>(it), t - it.tile0, lds);
+        adi_rows_seg<T, NT>(line_args<T>(it), it.ctrl, t - it.tile0, lds);
         __syncthreads();
     }
 }
 
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void k_batch_adi_cols_seg(const BatchItem* items, const int* tmap, int total) {
-    __shared__ T sh[5 * NT];
+    __shared__ T sh[5 * NT + kSegHead];
     for (int t = xcd_remap(blockIdx.x, gridDim.x); t < total; t += gridDim.x) {
         const BatchItem& it = items[tmap[t]];
-        if (it.ctrl->done) continue;
-        adi_cols_seg<T, NT>(line_args<T>(it), t - it.tile0, sh);
+        adi_cols_seg<T, NT>(line_args<T>(it), it.ctrl, t - it.tile0, sh);
         __syncthreads();
     }
 }
@@ -639,10 +726,11 @@ template <typename T>
 hipError_t launch_adi_rows_seg(const LineArgsT<T>& a, int lines, hipStream_t s) {
     const int W = seg_lines(0, a.m - 2);
     const int nt = (lines + W - 1) / W;
-    if (seg_code(0, a.m - 2) == 1)
-        k_adi_rows_seg<T, 256><<<xcd_pad(nt), 256, 0, s>>>(a, nt);
-    else
-        k_adi_rows_seg<T, 128><<<xcd_pad(nt), 128, 0, s>>>(a, nt);
+    switch (seg_code(0, a.m - 2)) {
+        case 0: k_adi_rows_seg<T, 64><<<xcd_pad(nt), 64, 0, s>>>(a, nt); break;
+        case 1: k_adi_rows_seg<T, 128><<<xcd_pad(nt), 128, 0, s>>>(a, nt); break;
+        default: k_adi_rows_seg<T, 256><<<xcd_pad(nt), 256, 0, s>>>(a, nt); break;
+    }
     return hipGetLastError();
 }
 
@@ -650,10 +738,12 @@ template <typename T>
 hipError_t launch_adi_cols_seg(const LineArgsT<T>& a, int lines, hipStream_t s) {
     const int W = seg_lines(1, a.n - 2);
     const int nt = (lines + W - 1) / W;
-    if (seg_code(1, a.n - 2) == 0)
-        k_adi_cols_seg<T, 256><<<xcd_pad(nt), 256, 0, s>>>(a, nt);
-    else
-        k_adi_cols_seg<T, 1024><<<xcd_pad(nt), 1024, 0, s>>>(a, nt);
+    switch (seg_code(1, a.n - 2)) {
+        case 0: k_adi_cols_seg<T, 64><<<xcd_pad(nt), 64, 0, s>>>(a, nt); break;
+        case 1: k_adi_cols_seg<T, 256><<<xcd_pad(nt), 256, 0, s>>>(a, nt); break;
+        case 2: k_adi_cols_seg<T, 512><<<xcd_pad(nt), 512, 0, s>>>(a, nt); break;
+        default: k_adi_cols_seg<T, 1024><<<xcd_pad(nt), 1024, 0, s>>>(a, nt); break;
+    }
     return hipGetLastError();
 }
 
@@ -679,37 +769,34 @@ hipError_t launch_zebra_lines(const LineArgsT<T>& a, int dir, hipStream_t s) {
 template hipError_t launch_zebra_lines<double>(const LineArgsT<double>&, int, hipStream_t);
 template hipError_t launch_zebra_lines<float>(const LineArgsT<float>&, int, hipStream_t);
 
+template <typename T>
+static void launch_batch_seg(int kind, int code, const BatchItem* items, const int* tmap, int total, int blocks,
+                             hipStream_t s) {
+    if (kind == BK_ADI_ROWS) {
+        switch (code) {
+            case 0: k_batch_adi_rows_seg<T, 64><<<blocks, 64, 0, s>>>(items, tmap, total); return;
+            case 1: k_batch_adi_rows_seg<T, 128><<<blocks, 128, 0, s>>>(items, tmap, total); return;
+            default: k_batch_adi_rows_seg<T, 256><<<blocks, 256, 0, s>>>(items, tmap, total); return;
+        }
+    }
+    switch (code) {
+        case 0: k_batch_adi_cols_seg<T, 64><<<blocks, 64, 0, s>>>(items, tmap, total); return;
+        case 1: k_batch_adi_cols_seg<T, 256><<<blocks, 256, 0, s>>>(items, tmap, total); return;
+        case 2: k_batch_adi_cols_seg<T, 512><<<blocks, 512, 0, s>>>(items, tmap, total); return;
+        default: k_batch_adi_cols_seg<T, 1024><<<blocks, 1024, 0, s>>>(items, tmap, total); return;
+    }
+}
+
 hipError_t launch_batch_adi(int kind, int flags, int dt, const BatchItem* items, const int* tmap, int total,
                             int blocks, hipStream_t s) {
     if (total <= 0) return hipSuccess;
     if (flags & ADI_SEG) {
         blocks = xcd_pad(blocks);
         const int code = (flags >> ADI_CODE_SHIFT) & 3;
-        if (kind == BK_ADI_ROWS) {
-            if (dt == 0) {
-                if (code == 1)
-                    k_batch_adi_rows_seg<double, 256><<<blocks, 256, 0, s>>>(items, tmap, total);
-                else
-                    k_batch_adi_rows_seg<double, 128><<<blocks, 128, 0, s>>>(items, tmap, total);
-            } else {
-                if (code == 1)
-                    k_batch_adi_rows_seg<float, 256><<<blocks, 256, 0, s>>>(items, tmap, total);
-                else
-                    k_batch_adi_rows_seg<float, 128><<<blocks, 128, 0, s>>>(items, tmap, total);
-            }
-        } else {
-            if (dt == 0) {
-                if (code == 0)
-                    k_batch_adi_cols_seg<double, 256><<<blocks, 256, 0, s>>>(items, tmap, total);
-                else
-                    k_batch_adi_cols_seg<double, 1024><<<blocks, 1024, 0, s>>>(items, tmap, total);
-            } else {
-                if (code == 0)
-                    k_batch_adi_cols_seg<float, 256><<<blocks, 256, 0, s>>>(items, tmap, total);
-                else
-                    k_batch_adi_cols_seg<float, 1024><<<blocks, 1024, 0, s>>>(items, tmap, total);
-            }
-        }
+        if (dt == 0)
+            launch_batch_seg<double>(kind, code, items, tmap, total, blocks, s);
+        else
+            launch_batch_seg<float>(kind, code, items, tmap, total, blocks, s);
         return hipGetLastError();
     }
     if (dt != 0) return hipErrorInvalidValue;   // the sequential solver is FP64 only

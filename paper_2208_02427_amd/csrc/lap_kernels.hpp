@@ -429,22 +429,43 @@ constexpr int SEG_G = 2 * kSegL;                  // response of a full block to
 constexpr int SEG_GL = 3 * kSegL;                 // the same for the last block
 constexpr int SEG_IPIVR = 4 * kSegL;              // reduced system: 1/pivot_p
 constexpr int SEG_CQR = 4 * kSegL + kSegMaxS;     // reduced system: E_R/pivot_p
-constexpr int SEG_E = 4 * kSegL + 2 * kSegMaxS;   // E, E_R
-constexpr int kSegTab = SEG_E + 2;
+constexpr int SEG_E = 4 * kSegL + 2 * kSegMaxS;   // E, E_R, scan reach (see seg_scan)
+constexpr int kSegTab = SEG_E + 3;
 __host__ __device__ constexpr int seg_count(int K) { return K <= 0 ? 0 : (K + kSegL + 1) / (kSegL + 1); }
-// Workgroup sizes: rows stage their lines in LDS (8.5 bytes per unknown), so
-// small workgroups keep several resident per CU; columns keep 8 or more
-// lines per workgroup so a wavefront's row accesses stay contiguous.
-// Size code c of a line length: rows use 128 << c threads (c = 0, 1),
-// columns 256 << c (c = 0 for lines of at most 4 blocks, else 2: 1024
-// threads, 4 or more lines per workgroup).
-__host__ __device__ constexpr int seg_code(int dir, int K) {
-    return dir == 0 ? (seg_count(K) <= 128 ? 0 : 1) : (seg_count(K) <= 4 ? 0 : 2);
+// Workgroup sizes, by the blocks S of a line (size code in two bits of the
+// operation flags).  Rows: one wavefront for lines of up to 64 blocks (its
+// barriers are free, and a small level spreads over as many CUs as it has
+// wavefronts), 128 and 256 threads for longer ones.  Columns: a
+// power-of-two number of lines per workgroup, at least 4 (64-byte rows), so
+// that a line of many blocks does not bind its neighbours to its CU: the
+// columns of 2049 x 1500 are 256 workgroups of 4 lines (512 threads), where
+// 1024 threads and 10 lines left 153 of 256 CUs idle.  FP64, per launch:
+// columns 21 -> 16.1 us, rows 20 -> 12.6 us (with the pair loads, the staged
+// table and the shortened scans of adi_kernels.hip).
+// A merged launch takes 512 threads for every column line it can: grids of
+// different sizes then share one launch (three otherwise, each too small to
+// fill the device).
+__host__ __device__ constexpr int seg_code(int dir, int K, bool merged = false) {
+    const int S = seg_count(K);
+    if (dir == 0) return S <= 64 ? 0 : S <= 128 ? 1 : 2;
+    if (merged) return S <= 128 ? 2 : 3;
+    return S <= 8 ? 0 : S <= 32 ? 1 : S <= 128 ? 2 : 3;
 }
-__host__ __device__ constexpr int seg_threads(int dir, int code) { return (dir == 0 ? 128 : 256) << code; }
-// lines per workgroup of the segmented kernels (one thread per block of a line)
-__host__ __device__ constexpr int seg_lines(int dir, int K) {
-    return seg_threads(dir, seg_code(dir, K)) / seg_count(K);
+__host__ __device__ constexpr int seg_threads(int dir, int code) {
+    if (dir == 0) return 64 << code;
+    return code == 0 ? 64 : 128 << code;
+}
+// lines per workgroup of NT threads of the segmented kernels (one thread per
+// block of a line)
+__host__ __device__ constexpr int seg_lines_of(int dir, int K, int NT) {
+    const int w = NT / seg_count(K);
+    if (dir == 0) return w;
+    int p = 1;
+    while (2 * p <= w) p *= 2;
+    return p;
+}
+__host__ __device__ constexpr int seg_lines(int dir, int K, bool merged = false) {
+    return seg_lines_of(dir, K, seg_threads(dir, seg_code(dir, K, merged)));
 }
 // q / d for 0 <= q < 2^20, 1 <= d <= 2^12, through single precision: the
 // quotient's fractional part is at least 0.5 / d away from an integer, far

@@ -2929,7 +2929,7 @@ BatchItem make_item(lap_grid* g, const Op& op, const lap_opts& o, size_t nplan) 
             const int span = op.kind == OP_ADI_ROWS ? L.n - 2 : L.m - 2;
             const int lines = span >= first ? (span - first) / 2 + 1 : 0;
             int per = op.kind == OP_ADI_ROWS ? kRowTile : kBlock;
-            if (op.flags & ADI_SEG) per = op.kind == OP_ADI_ROWS ? seg_lines(0, L.m - 2) : seg_lines(1, L.n - 2);
+            if (op.flags & ADI_SEG) per = op.kind == OP_ADI_ROWS ? seg_lines(0, L.m - 2) : seg_lines(1, L.n - 2, true);
             t.ntiles = (lines + per - 1) / per;
             break;
         }
@@ -3033,6 +3033,10 @@ lap_status get_plan(lap_ctx* c, const std::vector<lap_grid*>& gs, const std::vec
         lap_opts ok = o;
         if (grid_omega) ok.omega = gs[k]->batch_omega;
         plan_step(gs[k], ok, steps[k], PART_ALL, ops);
+        for (Op& op : ops)   // merged column lines share workgroup sizes (seg_code)
+            if (op.kind == OP_ADI_COLS && (op.flags & ADI_SEG))
+                op.flags = (op.flags & ~(3 << ADI_CODE_SHIFT)) |
+                           (seg_code(1, gs[k]->geo[op.level].n - 2, true) << ADI_CODE_SHIFT);
         for (size_t q = 1; q < ops.size(); ++q)
             if (ops[q].key <= ops[q - 1].key)   // merging by key must keep each grid's own order
                 return fail(LAP_EINVAL, "internal error: operation keys out of order");
