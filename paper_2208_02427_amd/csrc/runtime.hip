@@ -1629,7 +1629,10 @@ lap_status init_ctrl(lap_grid* g, const lap_opts& o, int step) {
 // sweeps, its restriction and the rest of its cycle are never enqueued;
 // otherwise the full step follows and repeats the same test (same norms,
 // same control block), so results and counts do not depend on probing.
-lap_status drive(lap_grid* g, int max_steps, const std::function<hipError_t(int)>& step, Ctrl& out,
+//
+// `step` sets *last when the test it enqueued ends the solve whatever it
+// finds (max_iter reached): nothing is enqueued behind it.
+lap_status drive(lap_grid* g, int max_steps, const std::function<hipError_t(int, bool*)>& step, Ctrl& out,
                  const std::function<hipError_t(int, bool*)>* probe = nullptr) {
     lap_ctx* c = g->ctx;
     int polled = -1;                 // last step whose control block was read
@@ -1673,8 +1676,10 @@ lap_status drive(lap_grid* g, int max_steps, const std::function<hipError_t(int)
             }
         }
         c->rec_step = s;
-        hipError_t e = step(s);
+        bool last = false;
+        hipError_t e = step(s, &last);
         if (e != hipSuccess) return fail(LAP_EHIP, std::string("kernel launch: ") + hipGetErrorString(e));
+        if (last) break;
         HIPCHK(hipMemcpyAsync(&c->pinned[s & 1], g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(hipEventRecord(c->poll_ev[s & 1], c->stream));
         if (s >= 1 && polled < s - 1) HIPCHK(poll(s - 1));
@@ -1812,6 +1817,10 @@ bool use_graph(lap_grid* g, const lap_opts& o) {
 }
 
 int ctrl_step(const lap_opts& o) { return (o.method == LAP_MG) ? 1 : o.check_every; }
+
+// Whether the test that outer step s opens with ends the solve whatever it
+// finds: the iterate has seen max_iter iterations.
+bool test_is_last(const lap_opts& o, int s) { return (int64_t)s * ctrl_step(o) >= o.max_iter; }
 
 // Per-solve set-up of one grid; init = false leaves the control block to the
 // caller (a batch resets all of them in one launch).
@@ -2086,7 +2095,14 @@ lap_status solve_one(lap_grid* g, const lap_opts& o, lap_info* info) {
         *did = !ops.empty();
         return ops.empty() ? hipSuccess : exec_ops(g, ops);
     };
-    st = drive(g, max_steps(o) + 1, [&](int) -> hipError_t { return step(g, o); }, h, &probe);
+    // a step that opens at max_iter ends with its test: only that is enqueued
+    // (200 SOR sweeps or 20 ADI iterations on a 3-megapixel grid otherwise drain
+    // up to two check blocks of launches that exit at once, 80 of 160 for ADI)
+    const auto enqueue = [&](int, bool* last) -> hipError_t {
+        *last = test_is_last(o, g->step_idx);
+        return step(g, o, *last ? PART_HEAD : PART_ALL);
+    };
+    st = drive(g, max_steps(o) + 1, enqueue, h, &probe);
     if (c->timing && st == LAP_OK) c->drop_speculative(c->rec_solve, h.checks - 1);
     c->rec_solve = -1;
     if (st != LAP_OK) return st;
@@ -3001,12 +3017,12 @@ int kclass_of(const Op& op) {
 // grid_omega: each grid's smoother relaxation is its own (lap_grid_set_omega)
 // instead of o.omega.
 lap_status get_plan(lap_ctx* c, const std::vector<lap_grid*>& gs, const std::vector<int>& steps, const lap_opts& o,
-                    lap_ctx::Plan** out, bool grid_omega = false) {
+                    lap_ctx::Plan** out, bool grid_omega = false, int part = PART_ALL) {
     std::string key;
     {
         char buf[96];
-        snprintf(buf, sizeof buf, "%d:%d:%d:%d:%d:%d:%d:%d:%.17g|", o.method, o.precision, o.smoother, o.nu1, o.nu2,
-                 o.check_every, o.adi_form, o.inner, o.omega);
+        snprintf(buf, sizeof buf, "%d:%d:%d:%d:%d:%d:%d:%d:%d:%.17g|", o.method, o.precision, o.smoother, o.nu1, o.nu2,
+                 o.check_every, o.adi_form, o.inner, part, o.omega);
         key = buf;
         for (size_t k = 0; k < gs.size(); ++k) {
             const int par = (o.method == LAP_MG && o.precision == LAP_MIXED)
@@ -3032,7 +3048,7 @@ lap_status get_plan(lap_ctx* c, const std::vector<lap_grid*>& gs, const std::vec
         std::vector<Op> ops;
         lap_opts ok = o;
         if (grid_omega) ok.omega = gs[k]->batch_omega;
-        plan_step(gs[k], ok, steps[k], PART_ALL, ops);
+        plan_step(gs[k], ok, steps[k], part, ops);
         for (Op& op : ops)   // merged column lines share workgroup sizes (seg_code)
             if (op.kind == OP_ADI_COLS && (op.flags & ADI_SEG))
                 op.flags = (op.flags & ~(3 << ADI_CODE_SHIFT)) |
@@ -3319,7 +3335,8 @@ extern "C" lap_status lap_solve_batch(lap_ctx* c, lap_grid* const* grids, int32_
         lap_ctx::Plan* p = nullptr;
         c->rec_step = r;
         for (int k = 0; k < count; ++k) steps[k] = r;
-        lap_status st = get_plan(c, all, steps, *o, &p);
+        const bool last = test_is_last(*o, r);   // every grid's test ends its solve: no round follows
+        lap_status st = get_plan(c, all, steps, *o, &p, false, last ? PART_HEAD : PART_ALL);
         if (st != LAP_OK) return st;
         hipError_t e = run_plan(c, p, o->use_graph != 0);
         if (e != hipSuccess) return fail(LAP_EHIP, std::string("batch launch: ") + hipGetErrorString(e));
@@ -3331,6 +3348,10 @@ extern "C" lap_status lap_solve_batch(lap_ctx* c, lap_grid* const* grids, int32_
         if (r >= 1) {
             st = absorb(r - 1);
             if (st != LAP_OK) return st;
+        }
+        if (last) {
+            ++r;
+            break;
         }
     }
     if (r >= 1 && decided < 0) {
