@@ -380,7 +380,7 @@ struct PaperArgs {
 };
 size_t paper_lds_bytes(int m, int n);
 hipError_t paper_set_lds_limit(int bytes);
-hipError_t launch_paper(const PaperArgs& a, hipStream_t s);
+hipError_t launch_paper(const PaperArgs& a, int lds_max, hipStream_t s);
 
 // ---- ADI (adi_kernels.hip) ----
 // T: element type of the field (the sequential solver is FP64 only; the

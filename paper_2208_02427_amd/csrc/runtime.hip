@@ -2057,7 +2057,7 @@ lap_status solve_paper(lap_grid* g, const lap_opts& o, lap_info* info) {
     a.tol = o.tol;
     a.max_iter = o.max_iter;
     lap_ctx* cx = g->ctx;
-    HIPCHK(cx->timed(KC_PAPER, true, 0.0, [&]() { return launch_paper(a, cx->stream); }));
+    HIPCHK(cx->timed(KC_PAPER, true, 0.0, [&]() { return launch_paper(a, cx->lds_max, cx->stream); }));
     Ctrl h{};
     HIPCHK(hipMemcpyAsync(&h, g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, cx->stream));
     HIPCHK(hipStreamSynchronize(cx->stream));
