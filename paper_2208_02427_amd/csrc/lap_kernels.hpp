@@ -280,11 +280,20 @@ struct CoarseArgs {
 // below it are internal to one launch.
 constexpr int kMaxSub = 16;
 constexpr int kSubBlock = 1024;
+// 2 x 2 patches of the top level a thread may hold: about what LDS takes
+// (FP64 129 x 65: 2048 patches, FP32 129 x 129: 4096)
+template <typename T> constexpr int kSubPatches = sizeof(T) == 8 ? 2 : 4;
+// stride of the top level's planes (one zero entry behind the patches)
+__host__ __device__ constexpr int sub_top_stride(int npt) { return npt * kSubBlock + 1; }
+// the coarsest inverse of at most this many unknowns is staged in LDS
+constexpr int kSubInvMax = 64;
 
 template <typename T>
 struct SubLevel {
-    int m, n;          // level size (LDS pitch m)
-    int ou, ob;        // LDS offsets (elements of T) of the level's u and b
+    int m, n;          // level size
+    int ou, ob;        // LDS offsets (elements of T) of the level's u and b: four planes of patches
+                       // each (u with a zero entry behind every plane), the coarsest level plain
+                       // arrays; the top's b stays in registers
     T cx, cy, d, inv_d;
 };
 
@@ -295,8 +304,12 @@ struct SubtreeArgs {
     int P;
     int nlev, nu1, nu2;
     T omega;
-    int lds_elems;       // elements of T for all levels' u and b
-    int lds_bytes;       // dynamic LDS of the launch (levels + coarse rhs)
+    int orr;             // LDS offset of the residual planes (three of the top's patches)
+    int lds_elems;       // elements of T before the coarse right-hand side
+    int inv_lds;         // nonzero: the coarsest inverse is staged behind that right-hand side
+    int npt;             // patches of the top level per thread of kSubBlock (1, 2 or 4)
+    int threads;         // threads that serve the top level's patches (a multiple of 64)
+    int lds_bytes;       // dynamic LDS of the launch
     const double* minv;  // coarsest factor (dense inverse or separable), see CoarseArgs
     double* work;
     int bw, ifast;
@@ -316,7 +329,9 @@ template <typename T> hipError_t launch_subtree(const SubtreeArgs<T>& a, hipStre
 // zero / + prolongation / with norms, result optionally restricted (SW_RESTRICT)
 template <typename T> hipError_t launch_fused(const SweepArgs<T>& a, int flags, hipStream_t s);
 // merged subtree launch: one workgroup per item, items[k].sub -> SubtreeArgs<T> in device memory
-hipError_t launch_batch_subtree(int dt, const struct BatchItem* items, int count, int lds_bytes, hipStream_t s);
+// (npt, threads, lds_bytes: the largest of the items)
+hipError_t launch_batch_subtree(int dt, const struct BatchItem* items, int count, int npt, int threads, int lds_bytes,
+                                hipStream_t s);
 // allow dynamic LDS up to `bytes` for the subtree kernels (once per device)
 hipError_t subtree_set_lds_limit(int bytes);
 // Sum the per-tile partials in a fixed order and run the stopping test.

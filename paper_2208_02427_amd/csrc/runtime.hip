@@ -553,12 +553,20 @@ struct HierView {
     int sub_root = -1;         // level whose whole sub-V-cycle runs as one LDS-resident launch
 };
 
-// LDS bytes of a subtree rooted at level l: u and b of every level l..L-1
-// (pitch m), then the coarsest right-hand side in FP64 (dense coarsest solve)
+// Patches of a smoothed level and LDS bytes of a subtree rooted at level l:
+// the top's u and residual planes, u and b of the smoothed levels below, u
+// and b of the coarsest, then the coarsest right-hand side in FP64 (dense
+// coarsest solve).
+int64_t sub_patches(const LevelGeo& G) { return (int64_t)((G.m - 1) / 2) * ((G.n - 1) / 2); }
+int sub_npt(int64_t np) { return np <= kSubBlock ? 1 : np <= 2 * kSubBlock ? 2 : 4; }
+// npt: of the launch (a merged launch's largest), 0: the level's own.
 template <typename T>
-size_t subtree_lds(const std::vector<LevelGeo>& geo, int l) {
-    size_t e = 0;
-    for (size_t k = (size_t)l; k < geo.size(); ++k) e += 2 * (size_t)geo[k].m * (size_t)geo[k].n;
+size_t subtree_lds(const std::vector<LevelGeo>& geo, int l, int npt = 0) {
+    const size_t L = geo.size();
+    const int64_t top = sub_patches(geo[l]);
+    size_t e = 4 * (size_t)sub_top_stride(npt > 0 ? npt : sub_npt(top)) + 3 * (size_t)top;
+    for (size_t k = (size_t)l + 1; k + 1 < L; ++k) e += 8 * (size_t)sub_patches(geo[k]) + 4;
+    e += 2 * (size_t)geo.back().m * (size_t)geo.back().n;
     size_t bytes = (e * sizeof(T) + 7) / 8 * 8;
     const size_t N = geo.back().interior();
     if (N <= (size_t)kDenseCoarseMax) bytes += N * sizeof(double);
@@ -569,13 +577,21 @@ size_t subtree_lds(const std::vector<LevelGeo>& geo, int l) {
 // workgroup's LDS (and the context's node limit); -1 if none.  The root must
 // have a level below it, and at most kMaxSub levels may take part.
 template <typename T>
-int subtree_root(const lap_grid* g, int lmin) {
+int subtree_root(const lap_grid* g, int lmin, int nu1) {
     const lap_ctx* c = g->ctx;
     const int L = (int)g->geo.size();
     if (c->sub_max_nodes == 0) return -1;
     for (int l = std::max(lmin, L - kMaxSub); l < L - 1; ++l) {
         const LevelGeo& G = g->geo[l];
         if (c->sub_max_nodes > 0 && (int64_t)G.m * G.n > c->sub_max_nodes) continue;
+        // Patches a thread may hold.  Two, in FP64 on 129 x 65, take 4-5 us a cycle
+        // less than the level's two launches (257 x 129: 560 -> 528 us a solve); four, in
+        // FP32 on 129 x 129, what its launches take and save two dispatches (1025^2: 882 ->
+        // 860 us), but not at level 0, whose post-smoothing runs fused with the defect
+        // correction.  A V(0, nu) cycle in FP64 keeps the launches of a level of more than
+        // one patch a thread (3 us a cycle): the separate schedule it is checked against.
+        const int most = l == 0 ? std::min(2, kSubPatches<T>) : sizeof(T) == 8 && nu1 == 0 ? 1 : kSubPatches<T>;
+        if (sub_patches(G) > kSubBlock * most) continue;
         if (subtree_lds<T>(g->geo, l) <= (size_t)c->lds_max) return l;
     }
     return -1;
@@ -583,8 +599,9 @@ int subtree_root(const lap_grid* g, int lmin) {
 
 // Arguments of the subtree rooted at level l (u -> out, right-hand side b).
 template <typename T>
-SubtreeArgs<T> subtree_args(const lap_grid* g, int l, T* out, const T* b, double omega, int nus) {
+SubtreeArgs<T> subtree_args(const lap_grid* g, int l, T* out, const T* b, double omega, int nus, int npt = 0) {
     SubtreeArgs<T> a{};
+    a.npt = npt > 0 ? npt : sub_npt(sub_patches(g->geo[l]));
     const int L = (int)g->geo.size();
     a.out = out;
     a.b = b;
@@ -600,17 +617,29 @@ SubtreeArgs<T> subtree_args(const lap_grid* g, int l, T* out, const T* b, double
         SubLevel<T>& v = a.lv[k];
         v.m = G.m;
         v.n = G.n;
+        const bool coarsest = k == a.nlev - 1;
+        const int np = (int)sub_patches(G);
         v.ou = off;
-        off += G.m * G.n;
+        off += coarsest ? G.m * G.n : 4 * (k == 0 ? sub_top_stride(a.npt) : np + 1);
         v.ob = off;
-        off += G.m * G.n;
+        if (k > 0) off += coarsest ? G.m * G.n : 4 * np;
+        if (k == 0) {
+            a.orr = off;
+            off += 3 * np;
+        }
         v.cx = (T)c.cx;
         v.cy = (T)c.cy;
         v.d = (T)c.d;
         v.inv_d = (T)c.inv_d;
     }
     a.lds_elems = off;
-    a.lds_bytes = (int)subtree_lds<T>(g->geo, l);
+    a.lds_bytes = (int)subtree_lds<T>(g->geo, l, a.npt);
+    const size_t N = g->geo.back().interior();
+    if (g->coarse_bw == 0 && N <= (size_t)kSubInvMax && a.lds_bytes + N * N * 8 <= (size_t)g->ctx->lds_max) {
+        a.inv_lds = 1;
+        a.lds_bytes += (int)(N * N * 8);
+    }
+    a.threads = (int)std::min<int64_t>(kSubBlock, (sub_patches(g->geo[l]) + 63) / 64 * 64);
     a.minv = g->minv;
     a.work = g->coarse_work;
     a.bw = g->coarse_bw;
@@ -993,7 +1022,7 @@ int plan_vcycle(lap_grid* g, HierView<T>& H, int l, const lap_opts& o, bool norm
     const bool tail = !split || part != PART_HEAD;
     T* U[2] = {H.u0[l], H.u1[l]};
     const T* b = H.b[l];
-    if (zero_start && l == H.sub_root && l < L - 1) {
+    if (zero_start && H.sub_root >= 0 && l >= H.sub_root && l < L - 1) {
         // the whole sub-V-cycle in one launch; its result lands where the
         // multi-launch schedule would leave it
         const int ri = vcycle_result_index(g->ctx, o);
@@ -1072,7 +1101,7 @@ int plan_vcycle(lap_grid* g, HierView<T>& H, int l, const lap_opts& o, bool norm
     return cur;
 }
 
-HierView<double> view64(lap_grid* g) {
+HierView<double> view64(lap_grid* g, int nu1) {
     HierView<double> H;
     const int L = (int)g->geo.size();
     H.u0.resize(L);
@@ -1087,11 +1116,11 @@ HierView<double> view64(lap_grid* g) {
         H.b[l] = g->l64[l].b;
     }
     H.zero_start0 = false;
-    H.sub_root = subtree_root<double>(g, 1);
+    H.sub_root = subtree_root<double>(g, 1, nu1);
     return H;
 }
 
-HierView<float> view32(lap_grid* g) {
+HierView<float> view32(lap_grid* g, int nu1) {
     HierView<float> H;
     const int L = (int)g->geo.size();
     H.u0.resize(L);
@@ -1103,7 +1132,7 @@ HierView<float> view32(lap_grid* g) {
         H.b[l] = g->l32[l].b;
     }
     H.zero_start0 = true;
-    H.sub_root = subtree_root<float>(g, 0);
+    H.sub_root = subtree_root<float>(g, 0, nu1);
     return H;
 }
 
@@ -1188,7 +1217,7 @@ bool postdef_ok(lap_grid* g, const lap_opts& o) {
     if (o.method != LAP_MG || o.precision != LAP_MIXED || !g->ctx->fuse || !g->rhs2) return false;
     if (o.smoother != LAP_SMOOTH_RB) return false;
     if (o.nu2 != 2 || o.nu1 < 2 || g->geo.size() < 2) return false;
-    return subtree_root<float>(g, 0) != 0;
+    return subtree_root<float>(g, 0, o.nu1) != 0;
 }
 
 // One outer step of the mixed loop: defect correction (adds the previous
@@ -1312,7 +1341,7 @@ void plan_mixed_step(lap_grid* g, const lap_opts& o, int s, int e_idx, int part,
     if (g->pdef) {
         float* R[2] = {g->l32[0].b, g->rhs2};
         const int par = s % 2;
-        HierView<float> H = view32(g);
+        HierView<float> H = view32(g, o.nu1);
         DeferredPost dp;
         if (part != PART_TAIL) {
             if (first) {
@@ -1364,7 +1393,7 @@ void plan_mixed_step(lap_grid* g, const lap_opts& o, int s, int e_idx, int part,
                             nullptr, 0.0);
         }
         if (part == PART_HEAD) return;
-        HierView<float> H = view32(g);
+        HierView<float> H = view32(g, o.nu1);
         H.u0[0] = z;
         plan_vcycle<float>(g, H, 0, o, false, PART_ALL, ops);
         return;
@@ -1385,7 +1414,7 @@ void plan_mixed_step(lap_grid* g, const lap_opts& o, int s, int e_idx, int part,
         ops.back().cycles = G.cycles;
     }
     if (part == PART_HEAD) return;
-    HierView<float> H = view32(g);
+    HierView<float> H = view32(g, o.nu1);
     plan_inner_cycles(g, o, H, ops, nullptr, G.later, G.one);
 }
 
@@ -1399,7 +1428,7 @@ void plan_mixed_step(lap_grid* g, const lap_opts& o, int s, int e_idx, int part,
 // in psi[0].
 void plan_fmg(lap_grid* g, const lap_opts& o, std::vector<Op>& ops) {
     const int L = (int)g->geo.size();
-    HierView<double> H = view64(g);
+    HierView<double> H = view64(g, o.nu1);
     long key = 50000;   // single-grid schedule: keys only need to increase
     auto boundary = [&](int l, bool set) {
         Op op{};
@@ -1422,7 +1451,7 @@ void plan_fmg(lap_grid* g, const lap_opts& o, std::vector<Op>& ops) {
         boundary(l + 1, false);
         HierView<double> R = H;
         R.root = l;
-        R.sub_root = subtree_root<double>(g, l + 1);
+        R.sub_root = subtree_root<double>(g, l + 1, o.nu1);
         plan_vcycle<double>(g, R, l, o, false, PART_ALL, ops);
     }
 }
@@ -1834,7 +1863,7 @@ lap_status prepare(lap_grid* g, const lap_opts& o, bool init = true) {
     g->e_idx = vcycle_result_index(g->ctx, o);
     if (o.method == LAP_MG && o.precision == LAP_MIXED && o.inner > 1 && !g->l32.empty()) {
         std::vector<Op> dry;   // where the step's first and last FP32 cycles leave the correction
-        g->e_idx = plan_inner_cycles(g, o, view32(g), dry, nullptr, nullptr, nullptr, &g->e1_idx);
+        g->e_idx = plan_inner_cycles(g, o, view32(g, o.nu1), dry, nullptr, nullptr, nullptr, &g->e1_idx);
     }
     // the two-buffer methods need both buffers equal when they start
     if (g->psi1_stale && o.method != LAP_ADI) {
@@ -1885,7 +1914,7 @@ lap_status prepare(lap_grid* g, const lap_opts& o, bool init = true) {
         hipError_t e;
         if (o.precision == LAP_FP64) {
             e = capture(g, key.c_str(), [&]() {
-                HierView<double> H = view64(g);
+                HierView<double> H = view64(g, o.nu1);
                 std::vector<Op> ops;
                 plan_vcycle<double>(g, H, 0, o, true, PART_ALL, ops);
                 return exec_ops(g, ops);
@@ -1921,7 +1950,7 @@ void plan_step(lap_grid* g, const lap_opts& o, int s, int part, std::vector<Op>&
                 }
                 if (part != PART_HEAD) plan_fmg(g, o, ops);
             } else if (o.precision == LAP_FP64) {
-                HierView<double> H = view64(g);
+                HierView<double> H = view64(g, o.nu1);
                 plan_vcycle<double>(g, H, 0, o, true, part, ops);
             } else {
                 plan_mixed_step(g, o, s, g->e_idx, part, ops);
@@ -2782,6 +2811,7 @@ struct MergedLaunch {
     bool fine;
     int count, total, blocks;
     int lds;                 // subtree: dynamic LDS bytes (largest item)
+    int npt, threads;        // subtree: patches per thread, threads (largest item)
     size_t off;              // first item in the plan's item array
     size_t toff;             // first entry in the plan's tile map
     double bytes;            // algorithmic bytes of the launch
@@ -3106,23 +3136,28 @@ lap_status get_plan(lap_ctx* c, const std::vector<lap_grid*>& gs, const std::vec
                 BatchItem it = gi.second;
                 it.tile0 = tile0;
                 if (L.kind == BK_SUBTREE) {
+                    if (L.npt == 0)   // the launch's kernel, so its plane stride, is the largest item's
+                        for (auto& gk : skv.second)
+                            L.npt = std::max(L.npt, sub_npt(sub_patches(gk.first.first->geo[gk.first.second.level])));
                     const Op& op = go.second;
                     const size_t off = p->subs.size();
-                    int lds = 0;
+                    const auto widest = [&L](const auto& a) {
+                        L.lds = std::max(L.lds, a.lds_bytes);
+                        L.threads = std::max(L.threads, a.threads);
+                    };
                     if (op.dt == 0) {
                         const auto a = subtree_args<double>(go.first, op.level, (double*)op.out,
-                                                            (const double*)op.f, op.omega, op.flags);
+                                                            (const double*)op.f, op.omega, op.flags, L.npt);
                         p->subs.resize(off + round_up(sizeof(a), 64));
                         std::memcpy(p->subs.data() + off, &a, sizeof(a));
-                        lds = a.lds_bytes;
+                        widest(a);
                     } else {
                         const auto a = subtree_args<float>(go.first, op.level, (float*)op.out, (const float*)op.f,
-                                                           op.omega, op.flags);
+                                                           op.omega, op.flags, L.npt);
                         p->subs.resize(off + round_up(sizeof(a), 64));
                         std::memcpy(p->subs.data() + off, &a, sizeof(a));
-                        lds = a.lds_bytes;
+                        widest(a);
                     }
-                    L.lds = std::max(L.lds, lds);
                     p->sub_of.push_back({p->items.size(), off});
                 }
                 if (L.kind != BK_COARSE && L.kind != BK_FINALIZE && L.kind != BK_SUBTREE) {
@@ -3197,7 +3232,8 @@ hipError_t run_plan_launches(lap_ctx* c, lap_ctx::Plan* p) {
         const MergedLaunch& L = p->launches[k];
         c->rec_head = k <= fin && fin < p->launches.size();
         HIPERR(c->timed(L.cls, L.fine, L.bytes, [&]() {
-            if (L.kind == BK_SUBTREE) return launch_batch_subtree(L.dt, p->dev + L.off, L.count, L.lds, c->stream);
+            if (L.kind == BK_SUBTREE) 
+                return launch_batch_subtree(L.dt, p->dev + L.off, L.count, L.npt, L.threads, L.lds, c->stream);
             const int32_t* tm = p->tmap_dev + L.toff;
             if (L.kind == BK_FUSED)
                 return launch_batch_fused(L.dt, L.flags, L.V, p->dev + L.off, tm, L.total, L.blocks, c->stream);

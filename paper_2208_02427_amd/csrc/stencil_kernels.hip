@@ -21,6 +21,7 @@
 #include <algorithm>
 
 #include "stencil_tiles.hpp"
+#include "subtree.hpp"
 
 namespace lap {
 
@@ -333,50 +334,81 @@ __device__ __forceinline__ double* subtree_rhs(T* s, int lds_elems) {
     return reinterpret_cast<double*>(s + ((lds_elems * (int)sizeof(T) + 7) / 8) * 8 / (int)sizeof(T));
 }
 
-template <typename T>
+template <typename T, int NPT>
 __global__ __launch_bounds__(kSubBlock) void k_subtree(SubtreeArgs<T> S) {
     if (S.ctrl != nullptr && S.ctrl->done) return;
     extern __shared__ double lds_raw[];
     T* s = reinterpret_cast<T*>(lds_raw);
-    subtree_block<T>(S, s, subtree_rhs(s, S.lds_elems));
+    subtree_block<T, NPT>(S, s, subtree_rhs(s, S.lds_elems));
 }
 
-template <typename T>
+template <typename T, int NPT>
 __global__ __launch_bounds__(kSubBlock) void k_batch_subtree(const BatchItem* items, int count) {
     const BatchItem& it = items[blockIdx.x];
     if (it.ctrl != nullptr && it.ctrl->done) return;
-    const SubtreeArgs<T>& S = *reinterpret_cast<const SubtreeArgs<T>*>(it.sub);
+    // read through the constant address space: the arguments are not written
+    // while the kernel runs, so they come in scalar registers
+    typedef const __attribute__((address_space(4))) SubtreeArgs<T> ConstArgs;
+    ConstArgs& S = *(ConstArgs*)(uintptr_t)it.sub;
     extern __shared__ double lds_raw[];
     T* s = reinterpret_cast<T*>(lds_raw);
-    subtree_block<T>(S, s, subtree_rhs(s, S.lds_elems));
+    subtree_block<T, NPT>(S, s, subtree_rhs(s, S.lds_elems));
+}
+
+// One kernel per patches-per-thread count (registers for its own only).
+template <typename T, typename F>
+static hipError_t with_npt(int npt, F&& f) {
+    if (npt == 1) return f(std::integral_constant<int, 1>());
+    if (npt == 2) return f(std::integral_constant<int, 2>());
+    if constexpr (kSubPatches<T> >= 4)
+        if (npt == 4) return f(std::integral_constant<int, 4>());
+    return hipErrorInvalidValue;
 }
 
 template <typename T>
 hipError_t launch_subtree(const SubtreeArgs<T>& a, hipStream_t s) {
-    if (a.nlev < 2 || a.nlev > kMaxSub) return hipErrorInvalidValue;
-    k_subtree<T><<<1, kSubBlock, a.lds_bytes, s>>>(a);
-    return hipGetLastError();
+    if (a.nlev < 2 || a.nlev > kMaxSub || a.threads < 64 || a.threads > kSubBlock) return hipErrorInvalidValue;
+    return with_npt<T>(a.npt, [&](auto n) {
+        k_subtree<T, decltype(n)::value><<<1, a.threads, a.lds_bytes, s>>>(a);
+        return hipGetLastError();
+    });
 }
 template hipError_t launch_subtree<double>(const SubtreeArgs<double>&, hipStream_t);
 template hipError_t launch_subtree<float>(const SubtreeArgs<float>&, hipStream_t);
 
-hipError_t launch_batch_subtree(int dt, const BatchItem* items, int count, int lds_bytes, hipStream_t s) {
-    if (count <= 0) return hipSuccess;
-    if (dt == 0)
-        k_batch_subtree<double><<<count, kSubBlock, lds_bytes, s>>>(items, count);
-    else
-        k_batch_subtree<float><<<count, kSubBlock, lds_bytes, s>>>(items, count);
-    return hipGetLastError();
+template <typename T>
+static hipError_t batch_subtree(const BatchItem* items, int count, int npt, int threads, int lds_bytes, hipStream_t s) {
+    return with_npt<T>(npt, [&](auto n) {
+        k_batch_subtree<T, decltype(n)::value><<<count, threads, lds_bytes, s>>>(items, count);
+        return hipGetLastError();
+    });
 }
 
-hipError_t subtree_set_lds_limit(int bytes) {
-    const void* fns[4] = {(const void*)k_subtree<double>, (const void*)k_subtree<float>,
-                          (const void*)k_batch_subtree<double>, (const void*)k_batch_subtree<float>};
-    for (const void* f : fns) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+hipError_t launch_batch_subtree(int dt, const BatchItem* items, int count, int npt, int threads, int lds_bytes,
+                                hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    return dt == 0 ? batch_subtree<double>(items, count, npt, threads, lds_bytes, s)
+                   : batch_subtree<float>(items, count, npt, threads, lds_bytes, s);
+}
+
+template <typename T>
+static hipError_t set_subtree_lds(int bytes) {
+    for (int npt = 1; npt <= kSubPatches<T>; npt *= 2) {
+        const hipError_t e = with_npt<T>(npt, [&](auto n) {
+            const hipError_t e1 = hipFuncSetAttribute((const void*)k_subtree<T, decltype(n)::value>,
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+            return e1 != hipSuccess ? e1
+                                    : hipFuncSetAttribute((const void*)k_batch_subtree<T, decltype(n)::value>,
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        });
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+hipError_t subtree_set_lds_limit(int bytes) {
+    const hipError_t e = set_subtree_lds<double>(bytes);
+    return e != hipSuccess ? e : set_subtree_lds<float>(bytes);
 }
 
 }  // namespace lap
