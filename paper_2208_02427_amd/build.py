@@ -18,8 +18,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "liblap.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["stencil_kernels.hip", "fused_kernels.hip", "batch_fused.hip", "adi_kernels.hip", "batch_kernels.hip",
-           "paper_kernels.hip", "runtime.hip"]
+SOURCES = ["fused_f64_v2.hip", "fused_f32_v2.hip", "batch_fused_f64.hip", "batch_fused_f32.hip", "fused_f64_v4.hip",
+           "fused_f32_v4.hip", "fused_f64_v1.hip", "fused_f32_v1.hip", "adi_kernels.hip", "stencil_kernels.hip",
+           "fused_kernels.hip", "batch_kernels.hip", "paper_kernels.hip", "runtime.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

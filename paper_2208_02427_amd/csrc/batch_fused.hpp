@@ -2,13 +2,19 @@
 // concatenated, a persistent grid of workgroups walking them (see
 // batch_kernels.hip), each tile running the same fused_tile as the
 // single-grid kernel with its grid's arguments, tiling and halo.
+#pragma once
+
 #include "fused_tiles.hpp"
 
 namespace lap {
 
 
+// The item table is read through the constant address space (nothing writes
+// it while a launch runs), so an item's arguments come in scalar registers.
+typedef const __attribute__((address_space(4))) BatchItem ConstItem;
+
 template <typename T, int FLS, int V>
-__device__ __forceinline__ void batch_fused_tile(const BatchItem& it, int lt, int lane) {
+__device__ __forceinline__ void batch_fused_tile(ConstItem& it, int lt, int lane) {
     SweepArgs<T> A{};
     A.uin = (const T*)it.in;
     A.uout = (T*)it.out;
@@ -59,9 +65,11 @@ template <typename T, int FLS, int V>
 __global__ __launch_bounds__(kBlock) void k_batch_fused(const BatchItem* items, const int* tmap, int total) {
     const int nw = gridDim.x * kWavesPerBlock;
     const int lane = threadIdx.x & 63;
-    for (int t = xcd_remap(blockIdx.x, gridDim.x) * kWavesPerBlock + (int)(threadIdx.x >> 6); t < total; t += nw) {
-        const BatchItem& it = items[tmap[t]];
-        if (it.ctrl->done) continue;
+    const auto* map = (const __attribute__((address_space(4))) int*)(uintptr_t)tmap;
+    ConstItem* table = (ConstItem*)(uintptr_t)items;
+    for (int t = xcd_remap(blockIdx.x, gridDim.x) * kWavesPerBlock + wave_in_block(); t < total; t += nw) {
+        ConstItem& it = table[map[t]];
+        if (__builtin_amdgcn_readfirstlane(it.ctrl->done)) continue;
         batch_fused_tile<T, FLS, V>(it, t - it.tile0, lane);
     }
 }
@@ -69,11 +77,13 @@ __global__ __launch_bounds__(kBlock) void k_batch_fused(const BatchItem* items, 
 // step flags without SW_F (the right-hand side is a per-grid runtime choice)
 #define LAP_BATCH_FUSED_FLAGS(X)                                                           \
     X(SW_TWO) X(SW_TWO | SW_ZERO) X(SW_TWO | SW_NORM) X(SW_TWO | SW_PROLONG) X(SW_RESTRICT) \
+    X(SW_TWO | SW_PROLONG | SW_ZERO)                                                       \
     X(SW_RESTRICT | SW_ZERO) X(SW_RESTRICT | SW_NORM) X(SW_RESTRICT | SW_TWO)              \
-    X(SW_RESTRICT | SW_TWO | SW_ZERO) X(SW_RESTRICT | SW_TWO | SW_NORM) X(SW_DEF | SW_PROLONG | SW_TWO)
-// FP32 only: the level-0 passes of the cycles after the first of a mixed step
-// of several cycles (residual in difference form; four-sweep passes)
-#define LAP_BATCH_FUSED_FLAGS32(X) \
+    X(SW_RESTRICT | SW_TWO | SW_ZERO) X(SW_RESTRICT | SW_TWO | SW_NORM)
+// FP32 only: the mixed loop's post-smoothing + defect pass, and the level-0
+// passes of the cycles after the first of a step of several cycles (residual
+// in difference form; four-sweep passes)
+#define LAP_BATCH_FUSED_FLAGS32(X) X(V == 2 ? SW_DEF | SW_PROLONG | SW_TWO : SW_UNUSED) \
     X(SW_RDIFF | SW_RESTRICT | SW_TWO) X(SW_RDIFF | SW_RESTRICT) X(SW_FOUR | SW_PROLONG | SW_RESTRICT | SW_RDIFF)
 
 template <typename T, int V>
@@ -83,7 +93,10 @@ static hipError_t launch_batch_fused_v(int fl, const BatchItem* items, const int
     switch (fl) {
 #define LAP_CASE(F)                                                       \
     case (F):                                                             \
-        k_batch_fused<T, (F), V><<<g, b, 0, s>>>(items, tmap, total);     \
+        if constexpr ((F) == SW_UNUSED)                                   \
+            return hipErrorInvalidValue;                                  \
+        else                                                              \
+            k_batch_fused<T, (F), V><<<g, b, 0, s>>>(items, tmap, total); \
         break;
         LAP_BATCH_FUSED_FLAGS(LAP_CASE)
         default:
@@ -101,7 +114,7 @@ static hipError_t launch_batch_fused_v(int fl, const BatchItem* items, const int
 }
 
 template <typename T>
-static hipError_t launch_batch_fused_t(int fl, int V, const BatchItem* items, const int* tmap, int total, int blocks,
+hipError_t launch_batch_fused_t(int fl, int V, const BatchItem* items, const int* tmap, int total, int blocks,
                                        hipStream_t s) {
     switch (V) {
         case 1: return launch_batch_fused_v<T, 1>(fl, items, tmap, total, blocks, s);
@@ -109,14 +122,6 @@ static hipError_t launch_batch_fused_t(int fl, int V, const BatchItem* items, co
         case 4: return launch_batch_fused_v<T, 4>(fl, items, tmap, total, blocks, s);
         default: return hipErrorInvalidValue;
     }
-}
-
-hipError_t launch_batch_fused(int dt, int step_flags, int V, const BatchItem* items, const int* tmap, int total,
-                              int blocks, hipStream_t s) {
-    if (total <= 0) return hipSuccess;
-    if (blocks < 1) blocks = 1;
-    return dt == 0 ? launch_batch_fused_t<double>(step_flags, V, items, tmap, total, blocks, s)
-                   : launch_batch_fused_t<float>(step_flags, V, items, tmap, total, blocks, s);
 }
 
 }  // namespace lap

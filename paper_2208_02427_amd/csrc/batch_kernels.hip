@@ -212,6 +212,18 @@ static hipError_t launch_batch_t(int kind, int fl, const BatchItem* items, const
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_batch_fused_t(int fl, int V, const BatchItem* items, const int* tmap, int total, int blocks,
+                                hipStream_t s);   // batch_fused.hpp
+
+hipError_t launch_batch_fused(int dt, int step_flags, int V, const BatchItem* items, const int* tmap, int total,
+                              int blocks, hipStream_t s) {
+    if (total <= 0) return hipSuccess;
+    if (blocks < 1) blocks = 1;
+    return dt == 0 ? launch_batch_fused_t<double>(step_flags, V, items, tmap, total, blocks, s)
+                   : launch_batch_fused_t<float>(step_flags, V, items, tmap, total, blocks, s);
+}
+
 hipError_t launch_batch(int kind, int dt, int step_flags, const BatchItem* items, const int* tmap, int count, int total,
                         int blocks,
                         hipStream_t s) {

@@ -81,6 +81,10 @@ inline Tiling make_tiling(int m, int n, int V, int ty, int target = 0, int H = 2
     return t;
 }
 
+// The halo of a tiling with V columns per lane: the fused passes (H > 2) store
+// whole lanes, so theirs is a multiple of V.
+inline int lane_halo(int H, int V) { return H > 2 ? (H + V - 1) / V * V : H; }
+
 // Fixed tiling of every kernel that produces norm partials (the first
 // pre-sweep with norms, residual norms, the FP64 defect correction): the
 // partial sums, and so the stopping decisions, then do not depend on the
@@ -182,6 +186,7 @@ enum : int {
     SW_FOUR = 1024,  // fused pass: four sweeps (a cycle's two post-smoothing sweeps after its bilinear
                      // correction, then the next cycle's two pre-smoothing sweeps, residual and full
                      // weighting: SW_PROLONG | SW_RESTRICT)
+    SW_UNUSED = 1 << 30,  // stands for a flag set a build of the kernels leaves out
 };
 
 template <typename T>
@@ -207,7 +212,6 @@ struct SweepArgs {
     const double* f64;
     T* rhs_out;
     double dcx, dcy, dd;
-    int nt;             // nonzero: the pass's row stores are nontemporal (streamed past the caches)
     // SW_DEF with rowpart: chunks of a multiple of kRowBlock rows walk downwards and the norm
     // partials are per (window, block of kRowBlock rows), at win * row_blocks(n) + (row - 1) /
     // kRowBlock, instead of per tile: the same sums whatever the chunk length (rp_off: set by the kernel)

@@ -405,7 +405,8 @@ struct lap_ctx {
     }
     Tiling tiling(int m, int n, int cls, int dt, int H = 2) const {
         const int sc = size_class((size_t)(m - 2) * (size_t)(n - 2));
-        return make_tiling(m, n, tileV[sc][cls][dt], tileTY[sc][cls][dt], tileT[sc][cls][dt], H);
+        const int V = tileV[sc][cls][dt];
+        return make_tiling(m, n, V, tileTY[sc][cls][dt], tileT[sc][cls][dt], lane_halo(H, V));
     }
 };
 
@@ -725,24 +726,12 @@ double sweep_bytes_per_node(int flags, int sz) {
     return per * sz;
 }
 
-// Whether a fused pass stores its rows nontemporally (past L2 and the
-// Infinity Cache).  Measured on an 8193^2 solve: for the FP64 multigrid
-// passes of every level it saves ~15 us per cycle on the coarser levels and
-// is even on the finest (7.00 -> 6.85 ms); the FP32 passes of the mixed loop
-// and the SOR passes (whose output the next pass reads at once) gain
-// nothing or lose, and keep ordinary stores, as do merged batch launches of
-// small grids.
-bool fused_nt(int dt, int flags) {
-    return dt == 0 && (flags & (SW_RESTRICT | SW_PROLONG)) != 0;
-}
-
 template <typename T>
 hipError_t enq_fused(lap_grid* g, int l, const T* in, T* out, const T* f, const T* ec, T* bc, double omega,
                      int flags) {
     SweepArgs<T> a = sweep_args<T>(g, l, in, out, f, ec, omega, (flags & SW_NORM) != 0);
     const LevelGeo& L = g->geo[l];
     a.bc = bc;
-    a.nt = fused_nt(dt_of<T>(), flags) ? 1 : 0;
     if (!(flags & SW_NORM)) a.tl = g->ctx->tiling(L.m, L.n, fused_class(flags), dt_of<T>(), fused_halo(flags));
     return g->ctx->timed(fused_class(flags), l == 0, sweep_bytes_per_node(flags, sizeof(T)) * nint(L),
                          [&]() { return launch_fused<T>(a, flags, g->ctx->stream); });
@@ -1089,7 +1078,10 @@ int plan_vcycle(lap_grid* g, HierView<T>& H, int l, const lap_opts& o, bool norm
     for (int k = 0; k < npost; ++k) {
         const int fl = fb | (pp.post[k] == 2 ? SW_TWO : 0);
         if (k == 0) {
-            push_op<T>(ops, key_post(l, k), OP_SWEEP, l, SW_PROLONG | fl, have_u ? U[cur] : nullptr,
+            // without pre-smoothing the pass starts from zero: the one-sweep kernel takes
+            // that from a null input, the fused pass from its flag
+            const int from = !have_u && is_fused(fl) ? SW_ZERO : 0;
+            push_op<T>(ops, key_post(l, k), OP_SWEEP, l, SW_PROLONG | from | fl, have_u ? U[cur] : nullptr,
                        U[have_u ? 1 - cur : 0], b, ec, nullptr, o.omega);
             cur = have_u ? 1 - cur : 0;
             have_u = true;
@@ -1203,7 +1195,6 @@ hipError_t enq_postdef(lap_grid* g, const Op& op, double omega) {
     a.dcx = c.cx;
     a.dcy = c.cy;
     a.dd = c.d;
-    a.nt = fused_nt(1, kPostDefFlags) ? 1 : 0;
     return g->ctx->timed(KC_DEFECT, true, postdef_bytes_per_node(g->f64 != nullptr) * nint(L), [&]() {
         return launch_fused<float>(a, kPostDefFlags, g->ctx->stream);
     });
@@ -3727,7 +3718,7 @@ extern "C" lap_status lap_autotune(lap_ctx* c, int32_t m, int32_t n, int32_t rep
                 const int H = (cls == KC_PRE || cls == KC_TWO || cls == KC_TWO_PLAIN || cls == KC_FOUR)
                                   ? fused_halo(base_flags(cls))
                                   : 2;
-                const Tiling t = make_tiling(m, n, cd.V, cd.ty, cd.tgt, H);
+                const Tiling t = make_tiling(m, n, cd.V, cd.ty, cd.tgt, lane_halo(H, cd.V));
                 double total = 0.0;
                 for (int fl0 : {0, (int)SW_F}) {
                     if (fl0 == 0 && cls != KC_SWEEP && cls != KC_TWO && cls != KC_TWO_PLAIN) continue;
