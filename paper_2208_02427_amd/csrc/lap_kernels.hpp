@@ -322,6 +322,19 @@ struct SubtreeArgs {
     SubLevel<T> lv[kMaxSub];
 };
 
+// A whole FP64 multigrid solve in one workgroup (mg_solve_block): the
+// hierarchy as a subtree whose top level is the grid (sub.out: the iterate, in
+// and out; sub.b: the source), the canonical tiling of its norms.
+constexpr int kMgSolveTiles = 64;
+constexpr int kMgSolveStatic = 2 * kMgSolveTiles * 8 + 256;   // LDS bytes of its partials and control block (rounded up)
+struct MgSolveArgs {
+    SubtreeArgs<double> sub;
+    Ctrl* ctrl;
+    Tiling tl;
+    int flip;            // odd row chunks of the norms are summed from above
+    int cycles;          // cycles of this launch, unless the test ends the solve before
+};
+
 // ---- launchers (stencil_kernels.hip) ----
 template <typename T> hipError_t launch_sweep(const SweepArgs<T>& a, int flags, hipStream_t s);
 template <typename T> hipError_t launch_restrict(const RestrictArgs<T>& a, hipStream_t s);
@@ -329,6 +342,7 @@ template <typename T> hipError_t launch_residual(const ResidualArgs<T>& a, hipSt
 template <typename T> hipError_t launch_coarse(const CoarseArgs<T>& a, hipStream_t s);
 hipError_t launch_defect(const DefectArgs& a, hipStream_t s);
 template <typename T> hipError_t launch_subtree(const SubtreeArgs<T>& a, hipStream_t s);
+hipError_t launch_mg_solve(const MgSolveArgs& a, hipStream_t s);
 // fused streaming pass (fused_kernels.hip): one or two sweeps (SW_TWO), input
 // zero / + prolongation / with norms, result optionally restricted (SW_RESTRICT)
 template <typename T> hipError_t launch_fused(const SweepArgs<T>& a, int flags, hipStream_t s);

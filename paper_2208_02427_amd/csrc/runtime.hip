@@ -560,12 +560,17 @@ struct HierView {
 // coarsest solve).
 int64_t sub_patches(const LevelGeo& G) { return (int64_t)((G.m - 1) / 2) * ((G.n - 1) / 2); }
 int sub_npt(int64_t np) { return np <= kSubBlock ? 1 : np <= 2 * kSubBlock ? 2 : 4; }
-// npt: of the launch (a merged launch's largest), 0: the level's own.
+// npt: of the launch (a merged launch's largest), 0: the level's own, -1: a
+// whole solve, whose top holds the iterate and its boundary.
+int64_t sub_top_planes(const LevelGeo& G, int npt) {
+    const int64_t np = sub_patches(G);
+    return npt < 0 ? np + (G.m - 1) / 2 + (G.n - 1) / 2 + 1 : sub_top_stride(npt > 0 ? npt : sub_npt(np));
+}
 template <typename T>
 size_t subtree_lds(const std::vector<LevelGeo>& geo, int l, int npt = 0) {
     const size_t L = geo.size();
     const int64_t top = sub_patches(geo[l]);
-    size_t e = 4 * (size_t)sub_top_stride(npt > 0 ? npt : sub_npt(top)) + 3 * (size_t)top;
+    size_t e = 4 * (size_t)sub_top_planes(geo[l], npt) + 3 * (size_t)top;
     for (size_t k = (size_t)l + 1; k + 1 < L; ++k) e += 8 * (size_t)sub_patches(geo[k]) + 4;
     e += 2 * (size_t)geo.back().m * (size_t)geo.back().n;
     size_t bytes = (e * sizeof(T) + 7) / 8 * 8;
@@ -602,7 +607,7 @@ int subtree_root(const lap_grid* g, int lmin, int nu1) {
 template <typename T>
 SubtreeArgs<T> subtree_args(const lap_grid* g, int l, T* out, const T* b, double omega, int nus, int npt = 0) {
     SubtreeArgs<T> a{};
-    a.npt = npt > 0 ? npt : sub_npt(sub_patches(g->geo[l]));
+    a.npt = npt > 0 ? npt : sub_npt(sub_patches(g->geo[l]));   // npt as in subtree_lds
     const int L = (int)g->geo.size();
     a.out = out;
     a.b = b;
@@ -621,7 +626,7 @@ SubtreeArgs<T> subtree_args(const lap_grid* g, int l, T* out, const T* b, double
         const bool coarsest = k == a.nlev - 1;
         const int np = (int)sub_patches(G);
         v.ou = off;
-        off += coarsest ? G.m * G.n : 4 * (k == 0 ? sub_top_stride(a.npt) : np + 1);
+        off += coarsest ? G.m * G.n : 4 * (k == 0 ? (int)sub_top_planes(G, npt) : np + 1);
         v.ob = off;
         if (k > 0) off += coarsest ? G.m * G.n : 4 * np;
         if (k == 0) {
@@ -634,9 +639,9 @@ SubtreeArgs<T> subtree_args(const lap_grid* g, int l, T* out, const T* b, double
         v.inv_d = (T)c.inv_d;
     }
     a.lds_elems = off;
-    a.lds_bytes = (int)subtree_lds<T>(g->geo, l, a.npt);
+    a.lds_bytes = (int)subtree_lds<T>(g->geo, l, npt);
     const size_t N = g->geo.back().interior();
-    if (g->coarse_bw == 0 && N <= (size_t)kSubInvMax && a.lds_bytes + N * N * 8 <= (size_t)g->ctx->lds_max) {
+    if (g->coarse_bw == 0 && N <= (size_t)kSubInvMax && a.lds_bytes + N * N * 8 <= (size_t)g->ctx->lds_max - kMgSolveStatic) {
         a.inv_lds = 1;
         a.lds_bytes += (int)(N * N * 8);
     }
@@ -2102,8 +2107,49 @@ lap_status solve_paper(lap_grid* g, const lap_opts& o, lap_info* info) {
     return res;
 }
 
+// Whether an FP64 multigrid solve of g runs as one launch of one workgroup
+// (mg_solve_block): the whole hierarchy fits its LDS, at most two patches of
+// the grid a thread, under the same switch and node limit as the subtree.
+bool mg_solve_ok(const lap_grid* g, const lap_opts& o) {
+    const lap_ctx* c = g->ctx;
+    const int L = (int)g->geo.size();
+    const LevelGeo& G = g->geo[0];
+    if (o.method != LAP_MG || o.precision != LAP_FP64 || o.smoother != LAP_SMOOTH_RB || o.fmg) return false;
+    if (L < 2 || L > kMaxSub || c->sub_max_nodes == 0) return false;
+    if (c->sub_max_nodes > 0 && (int64_t)G.m * G.n > c->sub_max_nodes) return false;
+    if (sub_patches(G) > kSubBlock * kSubPatches<double>) return false;
+    if (norm_tiling(G.m, G.n).ntiles > kMgSolveTiles) return false;
+    return subtree_lds<double>(g->geo, 0, -1) + kMgSolveStatic <= (size_t)c->lds_max;
+}
+
+lap_status solve_small(lap_grid* g, const lap_opts& o, lap_info* info) {
+    const double t0 = now_s();
+    lap_ctx* c = g->ctx;
+    lap_status st = init_ctrl(g, o, ctrl_step(o));
+    if (st != LAP_OK) return st;
+    MgSolveArgs a{};
+    a.sub = subtree_args<double>(g, 0, g->psi[0], g->f64, o.omega, o.nu1 | (o.nu2 << 8), -1);
+    a.ctrl = g->ctrl;
+    a.tl = norm_tiling(g->geo[0].m, g->geo[0].n);
+    std::vector<Op> head;   // how the launched solve would form its norms
+    plan_step(g, o, 0, PART_HEAD, head);
+    a.flip = !head.empty() && head[0].kind == OP_SWEEP && is_fused(head[0].flags) ? 1 : 0;
+    // a launch runs a bounded number of cycles (a few milliseconds); each
+    // next one starts with the test of the iterate the last one left
+    a.cycles = 500;
+    for (int64_t left = (int64_t)o.max_iter + 1; left > 0; left -= a.cycles) {
+        HIPCHK(c->timed(KC_SUBTREE, false, 16.0 * nint(g->geo[0]), [&]() { return launch_mg_solve(a, c->stream); }));
+        HIPCHK(hipMemcpyAsync(&c->pinned[2], g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(hipStreamSynchronize(c->stream));
+        if (c->pinned[2].done) break;
+    }
+    g->psi1_stale = true;   // psi[0] changed alone
+    return finish(g, o, c->pinned[2], t0, info);
+}
+
 lap_status solve_one(lap_grid* g, const lap_opts& o, lap_info* info) {
     if (is_paper_method(o.method)) return solve_paper(g, o, info);
+    if (mg_solve_ok(g, o)) return solve_small(g, o, info);
     const double t0 = now_s();
     lap_status st = prepare(g, o);
     if (st != LAP_OK) return st;

@@ -355,6 +355,12 @@ __global__ __launch_bounds__(kSubBlock) void k_batch_subtree(const BatchItem* it
     subtree_block<T, NPT>(S, s, subtree_rhs(s, S.lds_elems));
 }
 
+template <int NPT>
+__global__ __launch_bounds__(kSubBlock) void k_mg_solve(MgSolveArgs A) {
+    extern __shared__ double lds_raw[];
+    mg_solve_block<NPT>(A, lds_raw, subtree_rhs(lds_raw, A.sub.lds_elems));
+}
+
 // One kernel per patches-per-thread count (registers for its own only).
 template <typename T, typename F>
 static hipError_t with_npt(int npt, F&& f) {
@@ -375,6 +381,17 @@ hipError_t launch_subtree(const SubtreeArgs<T>& a, hipStream_t s) {
 }
 template hipError_t launch_subtree<double>(const SubtreeArgs<double>&, hipStream_t);
 template hipError_t launch_subtree<float>(const SubtreeArgs<float>&, hipStream_t);
+
+hipError_t launch_mg_solve(const MgSolveArgs& a, hipStream_t s) {
+    const SubtreeArgs<double>& S = a.sub;
+    if (S.nlev < 2 || S.nlev > kMaxSub || S.threads < 64 || S.threads > kSubBlock || a.tl.ntiles > kMgSolveTiles ||
+        a.tl.V != kNormPassV)
+        return hipErrorInvalidValue;
+    return with_npt<double>(S.npt, [&](auto n) {
+        k_mg_solve<decltype(n)::value><<<1, S.threads, S.lds_bytes, s>>>(a);
+        return hipGetLastError();
+    });
+}
 
 template <typename T>
 static hipError_t batch_subtree(const BatchItem* items, int count, int npt, int threads, int lds_bytes, hipStream_t s) {
@@ -407,8 +424,13 @@ static hipError_t set_subtree_lds(int bytes) {
 }
 
 hipError_t subtree_set_lds_limit(int bytes) {
-    const hipError_t e = set_subtree_lds<double>(bytes);
-    return e != hipSuccess ? e : set_subtree_lds<float>(bytes);
+    hipError_t e = set_subtree_lds<double>(bytes);
+    if (e == hipSuccess) e = set_subtree_lds<float>(bytes);
+    for (const void* f : {(const void*)k_mg_solve<1>, (const void*)k_mg_solve<2>})
+        // some of a workgroup's LDS is the kernel's own partials and control block
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes - kMgSolveStatic);
+    return e;
 }
 
 }  // namespace lap

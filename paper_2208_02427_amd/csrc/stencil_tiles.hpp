@@ -739,6 +739,35 @@ __device__ __forceinline__ void coarse_block(const CoarseArgs<T>& A, double* rhs
 }
 
 // ------------------------------------------------------------ norm finalise
+// The stopping test from the norms (sum of squares, max) of the iterate.
+__device__ __forceinline__ void decide_test(double sum, double m, Ctrl* ctrl, int mode) {
+    const double res = sqrt(sum);
+    const double r0 = ctrl->checks == 0 ? res : ctrl->r0;
+    const double rel = r0 > 0.0 ? res / r0 : 0.0;
+    const double q = ctrl->stop == 0 ? rel : m;
+    int status = 1;   // 1: the solve goes on
+    if (!isfinite(res) || !isfinite(m) || (r0 > 0.0 && res > 1e6 * r0))
+        status = -4;   // LAP_EDIVERGED
+    else if (q < ctrl->tol || res == 0.0)
+        status = 0;
+    else if (ctrl->iters >= ctrl->max_iter)
+        status = -3;   // LAP_ENOTCONV
+    // mode 2 (a probe of the test the next step opens with): only a test
+    // that ends the solve is recorded; otherwise that step repeats it
+    if (mode == 2 && status == 1) return;
+    ctrl->r0 = r0;
+    ctrl->res_l2 = res;
+    ctrl->res_inf = m;
+    ctrl->rel = rel;
+    ctrl->checks += 1;
+    if (status == 1) {
+        ctrl->iters += ctrl->step > 0 ? ctrl->step : 1;
+    } else {
+        ctrl->done = 1;
+        ctrl->status = status;
+    }
+}
+
 // One workgroup of kFinBlock threads: thread t sums partials t, t + kFinBlock,
 // ... in that order (loads issued four at a time), the waves reduce with a
 // fixed butterfly, and thread 0 adds the wave results in order, so the norm
@@ -783,31 +812,7 @@ __device__ __forceinline__ void finalize_block(const double* partials, int ntile
         out2[1] = m;
         return;
     }
-    const double res = sqrt(sum);
-    const double r0 = ctrl->checks == 0 ? res : ctrl->r0;
-    const double rel = r0 > 0.0 ? res / r0 : 0.0;
-    const double q = ctrl->stop == 0 ? rel : m;
-    int status = 1;   // 1: the solve goes on
-    if (!isfinite(res) || !isfinite(m) || (r0 > 0.0 && res > 1e6 * r0))
-        status = -4;   // LAP_EDIVERGED
-    else if (q < ctrl->tol || res == 0.0)
-        status = 0;
-    else if (ctrl->iters >= ctrl->max_iter)
-        status = -3;   // LAP_ENOTCONV
-    // mode 2 (a probe of the test the next step opens with): only a test
-    // that ends the solve is recorded; otherwise that step repeats it
-    if (mode == 2 && status == 1) return;
-    ctrl->r0 = r0;
-    ctrl->res_l2 = res;
-    ctrl->res_inf = m;
-    ctrl->rel = rel;
-    ctrl->checks += 1;
-    if (status == 1) {
-        ctrl->iters += ctrl->step > 0 ? ctrl->step : 1;
-    } else {
-        ctrl->done = 1;
-        ctrl->status = status;
-    }
+    decide_test(sum, m, ctrl, mode);
 }
 
 // Safety factor of the one-cycle prediction of a mixed step (the factor of a

@@ -52,9 +52,9 @@ struct SubGeo {
     T cx, cy, d, inv_d;
     T* u;                  // four planes
     template <typename L_>   // a SubLevel<T>, wherever it is stored
-    __device__ __forceinline__ SubGeo(T* s, const L_& L)
-        : W((L.m - 1) >> 1), H((L.n - 1) >> 1), np(W * H), stride(ST > 0 ? ST : np + 1), cx(L.cx), cy(L.cy),
-          d(L.d), inv_d(L.inv_d), u(s + L.ou) {}
+    __device__ __forceinline__ SubGeo(T* s, const L_& L, bool bnd = false)
+        : W((L.m - 1) >> 1), H((L.n - 1) >> 1), np(W * H), stride(ST > 0 ? ST : np + 1 + (bnd ? W + H : 0)),
+          cx(L.cx), cy(L.cy), d(L.d), inv_d(L.inv_d), u(s + L.ou) {}
     __device__ __forceinline__ T* plane(int k) const { return u + k * (ST > 0 ? ST : stride); }
     __device__ __forceinline__ int edge() const { return (ST > 0 ? ST : stride) - 1; }
 };
@@ -73,7 +73,7 @@ struct Patches {
     __device__ __forceinline__ bool xl(int q) const { return I[q] > 0; }
     __device__ __forceinline__ bool yl(int q) const { return J[q] > 0; }
 
-    __device__ __forceinline__ void place(const Geo& G, T om, int nthreads) {
+    __device__ __forceinline__ void place(const Geo& G, T om, int nthreads, bool bnd = false) {
         const float inv = 1.0f / (float)G.W;
         const int z = G.edge();
 #pragma unroll
@@ -83,9 +83,9 @@ struct Patches {
             J[q] = seg_div(p[q], inv);
             I[q] = p[q] - J[q] * G.W;
             kl[q] = on[q] && I[q] > 0 ? p[q] - 1 : z;
-            kr[q] = on[q] && I[q] < G.W - 1 ? p[q] + 1 : z;
+            kr[q] = on[q] && I[q] < G.W - 1 ? p[q] + 1 : on[q] && bnd ? G.np + J[q] : z;
             kd[q] = on[q] && J[q] > 0 ? p[q] - G.W : z;
-            ku[q] = on[q] && J[q] < G.H - 1 ? p[q] + G.W : z;
+            ku[q] = on[q] && J[q] < G.H - 1 ? p[q] + G.W : on[q] && bnd ? G.np + G.H + I[q] : z;
             wa[q] = xl(q) && yl(q) ? om : T(0);
             wb[q] = yl(q) ? om : T(0);
             wc[q] = xl(q) ? om : T(0);
@@ -387,6 +387,125 @@ __device__ __forceinline__ void subtree_block(const Args& S, T* s, double* rhs) 
             if (right) o[2 * (size_t)S.P + 2] = T(0);
         }
     }
+}
+
+// ---------------------------------------------------- whole small solves
+// An FP64 multigrid solve of a grid whose hierarchy fits LDS, in one launch of
+// one workgroup: the residual norms and the stopping test, then the V-cycle,
+// until the test ends the solve.  Launched pass by pass such a solve is all
+// dispatches, round trips to memory and the host's polls (25 x 17 chamber, 7
+// cycles: 464 us a call against 246 us).  The norms are those of the
+// launched solve bit for bit: the canonical tiles' lanes sum the same nodes in
+// the same order (rows of odd chunks from above where the first pass flips
+// them), and the partials are reduced by the same butterfly.
+template <int NPT>
+__device__ __forceinline__ void mg_solve_block(const MgSolveArgs& A, double* s, double* rhs) {
+    using T = double;
+    using V2 = typename VecT<T, 2>::type;
+    const SubtreeArgs<T>& S = A.sub;
+    const SubGeo<T, 0> G(s, S.lv[0], true);
+    const int m = S.lv[0].m, n = S.lv[0].n, nt = blockDim.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const size_t P = (size_t)S.P;
+    __shared__ double parts[2 * kMgSolveTiles];
+    __shared__ Ctrl ctrl;
+    Patches<T, NPT, 0> X;
+    X.place(G, S.omega, nt, true);
+    T *PA = G.plane(0), *PB = G.plane(1), *PC = G.plane(2), *PD = G.plane(3);
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+        if (!X.on[q]) continue;
+        const size_t at = (size_t)(2 * X.J[q]) * P + 2 * X.I[q];
+        const V2 u0 = *reinterpret_cast<const V2*>(S.out + at), u1 = *reinterpret_cast<const V2*>(S.out + at + P);
+        X.a[q] = u0.x;
+        X.b[q] = u0.y;
+        X.c[q] = u1.x;
+        X.d[q] = u1.y;
+        if (S.b != nullptr) {
+            const V2 f0 = *reinterpret_cast<const V2*>(S.b + at), f1 = *reinterpret_cast<const V2*>(S.b + at + P);
+            X.set_rhs(q, f0.x, f0.y, f1.x, f1.y);
+        }
+        const int k = X.p[q];
+        PA[k] = u0.x;
+        PB[k] = u0.y;
+        PC[k] = u1.x;
+        PD[k] = u1.y;
+    }
+    for (int J = threadIdx.x; J < G.H; J += nt) {
+        const int k = G.np + J;
+        PA[k] = S.out[(size_t)(2 * J) * P + m - 1];
+        PC[k] = S.out[(size_t)(2 * J + 1) * P + m - 1];
+        PB[k] = PD[k] = 0.0;
+    }
+    for (int I = threadIdx.x; I < G.W; I += nt) {
+        const int k = G.np + G.H + I;
+        PA[k] = S.out[(size_t)(n - 1) * P + 2 * I];
+        PB[k] = S.out[(size_t)(n - 1) * P + 2 * I + 1];
+        PC[k] = PD[k] = 0.0;
+    }
+    X.zero_edge(G);
+    if (threadIdx.x == 0) ctrl = *A.ctrl;
+    const double* minv = sub_stage_inverse(S, rhs);
+    __syncthreads();
+    // node (i, j) of the iterate
+    const auto at = [&](int i, int j) -> T {
+        const int I = i >> 1, J = j >> 1;
+        const int k = i == m - 1 ? G.np + J : j == n - 1 ? G.np + G.H + I : J * G.W + I;
+        return G.plane((i == m - 1 ? 0 : i & 1) + (j == n - 1 ? 0 : 2 * (j & 1)))[k];
+    };
+    const bool two = S.nlev == 2;
+    // at most A.cycles cycles a launch; the next one opens with the test that is due
+    for (int k = 0;; ++k) {
+        if (k == A.cycles) break;
+        for (int t = wave; t < A.tl.ntiles; t += nt >> 6) {
+            const int win = t % A.tl.nwin, chunk = t / A.tl.nwin;
+            const Cols<kNormPassV> c(win, lane, m, S.P, A.tl.H);
+            const int j0 = 1 + chunk * A.tl.ty, j1 = min(j0 + A.tl.ty - 1, n - 2);
+            const bool up = A.flip && (chunk & 1);
+            double s2 = 0.0, mx = 0.0;
+            for (int r = 0; r <= j1 - j0; ++r) {
+                const int j = up ? j1 - r : j0 + r;
+#pragma unroll
+                for (int e = 0; e < kNormPassV; ++e) {
+                    if (!c.cout[e]) continue;
+                    const int i = c.i0 + e;
+                    const T C = at(i, j);
+                    const T L = fma(-G.d, C, fma(G.cy, at(i, j - 1) + at(i, j + 1), G.cx * (at(i - 1, j) + at(i + 1, j))));
+                    const double v = (S.b != nullptr ? S.b[(size_t)j * P + i] : 0.0) - L;
+                    s2 = fma(v, v, s2);
+                    mx = fmax(mx, fabs(v));
+                }
+            }
+            s2 = wave_sum(s2);
+            mx = wave_max(mx);
+            if (lane == 0) {
+                parts[2 * t] = s2;
+                parts[2 * t + 1] = mx;
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            // k_finalize's first wavefront; its others have nothing to add
+            const bool have = lane < A.tl.ntiles;
+            const double sum = wave_sum(have ? 0.0 + parts[2 * lane] : 0.0);
+            const double mx = wave_max(have ? fmax(0.0, parts[2 * lane + 1]) : 0.0);
+            if (lane == 0) decide_test(0.0 + sum, fmax(0.0, mx), &ctrl, 0);
+        }
+        __syncthreads();
+        if (ctrl.done) break;
+        for (int q = 0; q < S.nu1; ++q) X.template sweep<false>(G, S.omega, false);
+        X.template restrict_to<false>(G, s + S.orr, s + S.lv[1].ob, S.lv[1].m, two, false);
+        sub_levels<T, false>(S, s, rhs, minv, 1, nt);
+        X.template prolong_add<false>(G, s + S.lv[1].ou, S.lv[1].m, two);
+        for (int q = 0; q < S.nu2; ++q) X.template sweep<false>(G, S.omega, false);
+    }
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+        if (!X.on[q]) continue;
+        T* o = S.out + (size_t)(2 * X.J[q]) * P + 2 * X.I[q];
+        *reinterpret_cast<V2*>(o) = V2{X.a[q], X.b[q]};
+        *reinterpret_cast<V2*>(o + P) = V2{X.c[q], X.d[q]};
+    }
+    if (threadIdx.x == 0) *A.ctrl = ctrl;
 }
 
 }  // namespace lap
