@@ -330,6 +330,9 @@ constexpr int kMgSolveStatic = 2 * kMgSolveTiles * 8 + 256;   // LDS bytes of it
 struct MgSolveArgs {
     SubtreeArgs<double> sub;
     Ctrl* ctrl;
+    Ctrl* host;          // its copy in pinned host memory
+    double tol;          // fresh: the control block starts from these (else from *ctrl)
+    int stop, max_iter, fresh;
     Tiling tl;
     int flip;            // odd row chunks of the norms are summed from above
     int cycles;          // cycles of this launch, unless the test ends the solve before
@@ -382,6 +385,8 @@ hipError_t launch_gather_ctrl(Ctrl* const* src, Ctrl* dst, int count, hipStream_
 hipError_t launch_stream_copy(const void* src, void* dst, size_t bytes, int blocks, hipStream_t s);
 // Dense m x n FP64 field (row pitch m) into pitched fields d0 and (if not NULL) d1.
 hipError_t launch_write_field(const double* src, double* d0, double* d1, int m, int n, int P, hipStream_t s);
+// Pitched field src into a dense m x n FP64 field.
+hipError_t launch_read_field(const double* src, double* dst, int m, int n, int P, hipStream_t s);
 // Copies of whole buffers (16-byte vectors), one launch for all of them.
 struct CopyItem {
     const double2* src;

@@ -323,6 +323,7 @@ struct lap_ctx {
     std::vector<lap_grid*> grids;
     std::map<std::string, std::vector<double>> inv_cache;
     Ctrl* pinned = nullptr;        // 4 host slots
+    Ctrl* pinned_dev = nullptr;      // the same slots as the device addresses them
     // batch readback: device pointer table, gathered control blocks, pinned copy
     int batch_cap = 0;
     Ctrl** batch_ptrs = nullptr;
@@ -457,8 +458,7 @@ struct lap_grid {
     // columns (2 * kSegTab values per level), FP64 and FP32
     double* ztab64 = nullptr;
     float* ztab32 = nullptr;
-    std::vector<double> zhost64;     // host copies (the uploads read them asynchronously)
-    std::vector<float> zhost32;
+    std::vector<char> upload;        // host copy of what grid creation uploads (alive while that copy is in flight)
     bool zebra_ok = false;
     bool pdef = false;               // the running mixed solve uses the post-smoothing + defect pass
     lap_opts batch_opts{};
@@ -476,12 +476,6 @@ namespace {
 // The control block whose done flag the kernels of the operation being
 // launched test: a gate of a mixed step while one is set, else the solve's.
 inline Ctrl* kctrl(const lap_grid* g) { return g->op_ctrl != nullptr ? g->op_ctrl : g->ctrl; }
-
-void* galloc(lap_grid* g, size_t bytes) {
-    void* p = g->ctx->arena.alloc(bytes);
-    if (p) g->allocs.push_back(p);
-    return p;
-}
 
 struct Footprint {
     size_t bytes = 0;
@@ -1709,8 +1703,8 @@ lap_status drive(lap_grid* g, int max_steps, const std::function<hipError_t(int,
         HIPCHK(hipEventRecord(c->poll_ev[s & 1], c->stream));
         if (s >= 1 && polled < s - 1) HIPCHK(poll(s - 1));
     }
+    HIPCHK(hipMemcpyAsync(&c->pinned[2], g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
-    HIPCHK(hipMemcpy(&c->pinned[2], g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost));
     out = c->pinned[2];
     return LAP_OK;
 }
@@ -2125,11 +2119,14 @@ bool mg_solve_ok(const lap_grid* g, const lap_opts& o) {
 lap_status solve_small(lap_grid* g, const lap_opts& o, lap_info* info) {
     const double t0 = now_s();
     lap_ctx* c = g->ctx;
-    lap_status st = init_ctrl(g, o, ctrl_step(o));
-    if (st != LAP_OK) return st;
     MgSolveArgs a{};
     a.sub = subtree_args<double>(g, 0, g->psi[0], g->f64, o.omega, o.nu1 | (o.nu2 << 8), -1);
     a.ctrl = g->ctrl;
+    a.host = c->pinned_dev + 2;
+    a.tol = o.tol;
+    a.stop = o.stop;
+    a.max_iter = o.max_iter;
+    a.fresh = 1;
     a.tl = norm_tiling(g->geo[0].m, g->geo[0].n);
     std::vector<Op> head;   // how the launched solve would form its norms
     plan_step(g, o, 0, PART_HEAD, head);
@@ -2139,8 +2136,8 @@ lap_status solve_small(lap_grid* g, const lap_opts& o, lap_info* info) {
     a.cycles = 500;
     for (int64_t left = (int64_t)o.max_iter + 1; left > 0; left -= a.cycles) {
         HIPCHK(c->timed(KC_SUBTREE, false, 16.0 * nint(g->geo[0]), [&]() { return launch_mg_solve(a, c->stream); }));
-        HIPCHK(hipMemcpyAsync(&c->pinned[2], g->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(hipStreamSynchronize(c->stream));
+        a.fresh = 0;
         if (c->pinned[2].done) break;
     }
     g->psi1_stale = true;   // psi[0] changed alone
@@ -2247,7 +2244,8 @@ lap_status lap_ctx_create(void* dev_arena, size_t arena_bytes, void* hip_stream,
         }
     }
     default_tilings(c);
-    if (hipHostMalloc((void**)&c->pinned, 4 * sizeof(Ctrl), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void**)&c->pinned, 4 * sizeof(Ctrl), hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer((void**)&c->pinned_dev, c->pinned, 0) != hipSuccess) {
         delete c;
         return fail(LAP_EHIP, "hipHostMalloc of the control slots failed");
     }
@@ -2353,11 +2351,16 @@ lap_status lap_grid_create_ex(lap_ctx* c, int32_t m, int32_t n, double dx, doubl
     g->has_f = source != nullptr;
     const size_t f0 = (size_t)n * g->P;
     const int L = (int)lv.size();
-    bool ok = true;
+    // one block of the arena, carved in order (the footprint adds the same sizes)
+    char* const block = (char*)c->arena.alloc(fp.bytes);
+    if (block) g->allocs.push_back(block);
+    bool ok = block != nullptr;
+    size_t carved = 0;
     auto A = [&](size_t bytes) -> void* {
-        void* p = galloc(g, bytes);
-        if (!p) ok = false;
-        return p;
+        void* p = block + carved;
+        carved += round_up(std::max<size_t>(bytes, 1), kAlign);
+        if (carved > fp.bytes) ok = false;
+        return ok ? p : nullptr;
     };
     g->psi[0] = (double*)A(f0 * 8);
     g->psi[1] = (double*)A(f0 * 8);
@@ -2407,8 +2410,8 @@ lap_status lap_grid_create_ex(lap_ctx* c, int32_t m, int32_t n, double dx, doubl
         factor = &c->inv_cache[key];
         g->minv = (double*)A(factor->size() * 8);
     }
-    std::vector<double>& z64 = g->zhost64;
-    std::vector<float>& z32 = g->zhost32;
+    std::vector<double> z64;
+    std::vector<float> z32;
     if (mg && zebra_fits(lv)) {
         g->zebra_ok = true;
         z64.assign((size_t)L * 2 * kSegTab, 0.0);
@@ -2439,21 +2442,27 @@ lap_status lap_grid_create_ex(lap_ctx* c, int32_t m, int32_t n, double dx, doubl
         return fail(LAP_ENOMEM, "arena exhausted");
     }
     hipStream_t s = c->stream;
-    for (void* p : g->allocs) {
-        // zero every buffer (padding included) so no kernel ever reads garbage
-        const size_t off = (size_t)((char*)p - c->arena.base);
-        const size_t sz = c->arena.used_[off];
-        if (hipMemsetAsync(p, 0, sz, s) != hipSuccess) {
-            lap_grid_destroy(g);
-            return fail(LAP_EHIP, "hipMemsetAsync failed");
-        }
+    // zero every buffer (padding included) so no kernel ever reads garbage
+    if (hipMemsetAsync(block, 0, fp.bytes, s) != hipSuccess) {
+        lap_grid_destroy(g);
+        return fail(LAP_EHIP, "hipMemsetAsync failed");
     }
     hipError_t e = launch_write_field(psi0, g->psi[0], g->psi[1], m, n, g->P, s);
     if (e == hipSuccess && source) e = launch_write_field(source, g->f64, nullptr, m, n, g->P, s);
-    if (e == hipSuccess && mg)
-        e = hipMemcpyAsync(g->minv, factor->data(), factor->size() * 8, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && g->ztab64) e = hipMemcpyAsync(g->ztab64, z64.data(), z64.size() * 8, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && g->ztab32) e = hipMemcpyAsync(g->ztab32, z32.data(), z32.size() * 4, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess && mg) {
+        // the coarsest factor and the line tables, adjacent in the block, in one copy
+        std::vector<char>& up = g->upload;
+        const auto put = [&](const void* dev, const void* host, size_t bytes) {
+            if (!dev) return;
+            const size_t at = (size_t)((const char*)dev - (const char*)g->minv);
+            if (up.size() < at + bytes) up.resize(at + bytes, 0);
+            std::memcpy(up.data() + at, host, bytes);
+        };
+        put(g->minv, factor->data(), factor->size() * 8);
+        put(g->ztab64, z64.data(), z64.size() * 8);
+        put(g->ztab32, z32.data(), z32.size() * 4);
+        e = hipMemcpyAsync(g->minv, up.data(), up.size(), hipMemcpyHostToDevice, s);
+    }
     if (e != hipSuccess) {
         lap_grid_destroy(g);
         return fail(LAP_EHIP, std::string("grid upload: ") + hipGetErrorString(e));
@@ -2484,8 +2493,7 @@ lap_status lap_grid_destroy(lap_grid* g) {
 lap_status lap_grid_read(lap_grid* g, double* dst) {
     if (!g) return fail(LAP_EINVAL, "grid is NULL");
     if (!dst) return fail(LAP_EINVAL, "dst is NULL");
-    HIPCHK(hipMemcpy2DAsync(dst, (size_t)g->m * 8, g->psi[0], (size_t)g->P * 8, (size_t)g->m * 8, g->n,
-                            hipMemcpyDeviceToDevice, g->ctx->stream));
+    HIPCHK(launch_read_field(g->psi[0], dst, g->m, g->n, g->P, g->ctx->stream));
     return LAP_OK;
 }
 

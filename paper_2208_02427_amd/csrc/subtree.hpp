@@ -208,6 +208,22 @@ struct Patches {
         sub_sync<WAVE>();
     }
 
+    // every node's residual into four planes R (boundary nodes': not used)
+    __device__ __forceinline__ void residuals(const Geo& G, T* R) {
+        const T *PA = G.plane(0), *PB = G.plane(1), *PC = G.plane(2), *PD = G.plane(3);
+        const auto res = [&](T f, T u, T W, T E, T S, T N) { return f - fma(-G.d, u, fma(G.cy, S + N, G.cx * (W + E))); };
+#pragma unroll
+        for (int q = 0; q < NPT; ++q) {
+            const T bw = PB[kl[q]], cs = PC[kd[q]], ce = PC[kr[q]], bn = PB[ku[q]];
+            const T ae = PA[kr[q]], an = PA[ku[q]], ds = PD[kd[q]], dw = PD[kl[q]];
+            if (!on[q]) continue;
+            R[p[q]] = res(fa[q], a[q], bw, b[q], cs, c[q]);
+            R[p[q] + G.np] = res(fb[q], b[q], a[q], ae, ds, d[q]);
+            R[p[q] + 2 * G.np] = res(fc[q], c[q], dw, d[q], a[q], an);
+            R[p[q] + 3 * G.np] = res(fd[q], d[q], c[q], ce, b[q], bn);
+        }
+    }
+
     // this level's right-hand side / iterate from the planes
     __device__ __forceinline__ void load_rhs(const Geo& G, const T* f) {
 #pragma unroll
@@ -394,7 +410,7 @@ __device__ __forceinline__ void subtree_block(const Args& S, T* s, double* rhs) 
 // one workgroup: the residual norms and the stopping test, then the V-cycle,
 // until the test ends the solve.  Launched pass by pass such a solve is all
 // dispatches, round trips to memory and the host's polls (25 x 17 chamber, 7
-// cycles: 464 us a call against 246 us).  The norms are those of the
+// cycles: 464 us a call against 219 us, 68 of them the launch).  The norms are those of the
 // launched solve bit for bit: the canonical tiles' lanes sum the same nodes in
 // the same order (rows of odd chunks from above where the first pass flips
 // them), and the partials are reduced by the same butterfly.
@@ -443,34 +459,41 @@ __device__ __forceinline__ void mg_solve_block(const MgSolveArgs& A, double* s, 
         PC[k] = PD[k] = 0.0;
     }
     X.zero_edge(G);
-    if (threadIdx.x == 0) ctrl = *A.ctrl;
+    if (threadIdx.x == 0) {
+        if (A.fresh) {
+            ctrl = Ctrl{};
+            ctrl.tol = A.tol;
+            ctrl.stop = A.stop;
+            ctrl.max_iter = A.max_iter;
+            ctrl.step = 1;
+        } else {
+            ctrl = *A.ctrl;
+        }
+    }
     const double* minv = sub_stage_inverse(S, rhs);
     __syncthreads();
-    // node (i, j) of the iterate
-    const auto at = [&](int i, int j) -> T {
-        const int I = i >> 1, J = j >> 1;
-        const int k = i == m - 1 ? G.np + J : j == n - 1 ? G.np + G.H + I : J * G.W + I;
-        return G.plane((i == m - 1 ? 0 : i & 1) + (j == n - 1 ? 0 : 2 * (j & 1)))[k];
-    };
     const bool two = S.nlev == 2;
     // at most A.cycles cycles a launch; the next one opens with the test that is due
     for (int k = 0;; ++k) {
         if (k == A.cycles) break;
+        // every node's residual into four planes (the last one in the next
+        // level's room, idle between cycles and larger), then the canonical
+        // tiles' sums: a lane adds its two columns row by row
+        X.residuals(G, s + S.orr);
+        __syncthreads();
         for (int t = wave; t < A.tl.ntiles; t += nt >> 6) {
             const int win = t % A.tl.nwin, chunk = t / A.tl.nwin;
             const Cols<kNormPassV> c(win, lane, m, S.P, A.tl.H);
             const int j0 = 1 + chunk * A.tl.ty, j1 = min(j0 + A.tl.ty - 1, n - 2);
-            const bool up = A.flip && (chunk & 1);
+            const int step = A.flip && (chunk & 1) ? -1 : 1;
+            const double* r = s + S.orr + min(max(c.i0 >> 1, 0), G.W - 1);   // column pair c.i0, c.i0 + 1
             double s2 = 0.0, mx = 0.0;
-            for (int r = 0; r <= j1 - j0; ++r) {
-                const int j = up ? j1 - r : j0 + r;
+#pragma unroll 4
+            for (int k = 0, j = step > 0 ? j0 : j1; k <= j1 - j0; ++k, j += step) {
+                const double* rj = r + 2 * (j & 1) * G.np + (j >> 1) * G.W;
 #pragma unroll
                 for (int e = 0; e < kNormPassV; ++e) {
-                    if (!c.cout[e]) continue;
-                    const int i = c.i0 + e;
-                    const T C = at(i, j);
-                    const T L = fma(-G.d, C, fma(G.cy, at(i, j - 1) + at(i, j + 1), G.cx * (at(i - 1, j) + at(i + 1, j))));
-                    const double v = (S.b != nullptr ? S.b[(size_t)j * P + i] : 0.0) - L;
+                    const double v = c.cout[e] ? rj[e * G.np] : 0.0;
                     s2 = fma(v, v, s2);
                     mx = fmax(mx, fabs(v));
                 }
@@ -505,7 +528,7 @@ __device__ __forceinline__ void mg_solve_block(const MgSolveArgs& A, double* s, 
         *reinterpret_cast<V2*>(o) = V2{X.a[q], X.b[q]};
         *reinterpret_cast<V2*>(o + P) = V2{X.c[q], X.d[q]};
     }
-    if (threadIdx.x == 0) *A.ctrl = ctrl;
+    if (threadIdx.x == 0) *A.ctrl = *A.host = ctrl;
 }
 
 }  // namespace lap
