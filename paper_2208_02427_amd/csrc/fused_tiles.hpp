@@ -124,7 +124,6 @@ struct FusedLane {
 
 // SW_DEF with norms per block of kRowBlock rows: the lanes' sums of up to
 // kRowPartBlocks blocks of each wavefront's chunk.
-constexpr int kRowPartBlocks = 4;
 __device__ __forceinline__ double* rowpart_slot(int block) {
     __shared__ double parts[kWavesPerBlock][kRowPartBlocks][2][64];
     return &parts[wave_in_block()][block][0][threadIdx.x & 63];

@@ -130,9 +130,12 @@ inline Tiling norm_tiling(int m, int n, int kind = NORM_PASS) {
     if (kind == NORM_POSTDEF) return make_tiling(m, n, 2, 0, 16384, kNormH, n > kPostDefShortRowsN ? 16 : 64);
     return make_tiling(m, n, kNormPassV, 0, kNormWaves, kNormH);
 }
-// Tiling of the post-smoothing + defect pass alone or in a merged launch.
-inline Tiling postdef_tiling(int m, int n, bool merged) {
-    if (postdef_rowpart(n)) return make_tiling(m, n, 2, merged ? 4 * kRowBlock : kRowBlock, 0, kNormH);
+// Blocks of rows a chunk of the post-smoothing + defect pass may hold.
+constexpr int kRowPartBlocks = 4;
+// Tiling of the post-smoothing + defect pass; rows per chunk (a multiple of
+// kRowBlock, at most kRowPartBlocks blocks) where the norms are per block.
+inline Tiling postdef_tiling(int m, int n, int rows) {
+    if (postdef_rowpart(n)) return make_tiling(m, n, 2, rows, 0, kNormH);
     return norm_tiling(m, n, NORM_POSTDEF);
 }
 // Norm partials a finalisation of this kind reduces.

@@ -1185,7 +1185,7 @@ hipError_t enq_postdef(lap_grid* g, const Op& op, double omega) {
     a.d = (float)c.d;
     a.inv_d = (float)c.inv_d;
     a.omega = (float)omega;
-    a.tl = postdef_tiling(L.m, L.n, false);
+    a.tl = postdef_tiling(L.m, L.n, kRowBlock);
     a.rowpart = postdef_rowpart(L.n) ? 1 : 0;
     a.psi_in = (const double*)op.in;
     a.psi_out = (double*)op.out;
@@ -2917,16 +2917,26 @@ int batch_kind(const Op& op) {
     return -1;
 }
 
-constexpr int kBatchMinRows = 32;
-// Four-sweep passes (halo 10) in plans of many grids: chunks of >= 64 rows
-// (512-grid ragged batch, four FP32 cycles per correction: 12.3 ms with 32,
-// 11.0 with 64, 11.2 with 128; four columns per lane 11.1-11.3)
-constexpr int kBatchFourMinRows = 64;
+// Rows per chunk of a merged pass in plans of many grids.  A wavefront's walk
+// down its chunk is what a launch with few of them waits for, the chunk's
+// halo rows (up to 11 for a two-sweep pass, 21 for four sweeps) what a launch
+// that fills the device pays: the chunks are as long as leaves the launch
+// about kBatchWaves wavefronts, between 8 rows (the halo) and 32 (64 with four
+// sweeps).  512-grid ragged batch (54.6 M nodes): 32 rows (16:
+// 16.0 against 15.4 ms); 48 grids (4.9 M nodes): 10 rows, a solve 7.2 -> 6.8 ms.
+constexpr int kBatchWaves = 4096;
+constexpr int kBatchRows[2] = {8, 32};
+constexpr int kBatchFourMaxRows = 64;
+int batch_rows(double nodes, int unit, int lo, int hi) {
+    const int r = (int)(nodes / (win_step(2, kNormH) * (double)kBatchWaves));
+    return std::min(hi, std::max(lo, (r + unit - 1) / unit * unit));
+}
 constexpr size_t kBatchManyGrids = 4;
 constexpr int kBatchV = 2;
 
 // Fill the item of grid g for operation op (tiling, geometry, coefficients).
-BatchItem make_item(lap_grid* g, const Op& op, const lap_opts& o, size_t nplan) {
+// nplan: grids of the plan; nodes: of all grids in the operation's launch.
+BatchItem make_item(lap_grid* g, const Op& op, const lap_opts& o, size_t nplan, double nodes) {
     lap_ctx* c = g->ctx;
     const LevelGeo& L = g->geo[op.level];
     const Coef k = coef(L.dx, L.dy);
@@ -2978,7 +2988,7 @@ BatchItem make_item(lap_grid* g, const Op& op, const lap_opts& o, size_t nplan) 
             it.e = op.zbuf;   // the FP32 buffer the defect correction sets to zero (zebra cycles)
             break;
         case OP_POSTDEF:
-            t = postdef_tiling(L.m, L.n, true);
+            t = postdef_tiling(L.m, L.n, batch_rows(nodes, kRowBlock, kRowBlock, kRowPartBlocks * kRowBlock));
             it.rowpart = postdef_rowpart(L.n) ? 1 : 0;
             it.e = (op.parity == 0 || op.parity == 1) ? g->l32[0].u[op.parity] : nullptr;
             it.f64 = g->f64;
@@ -3029,16 +3039,15 @@ BatchItem make_item(lap_grid* g, const Op& op, const lap_opts& o, size_t nplan) 
     }
     // The table's short row chunks (down to 2 rows) and narrow windows
     // minimise the latency of one grid's small level.  Inside a merged launch
-    // over several grids a chunk's halo rows (up to 11 for a fused pass)
-    // weigh more, so plans of 4 or more grids use chunks of >= 32 rows (>= 64
-    // for four-sweep passes), and every plan of 2 or more grids 2 columns per
-    // lane (one launch per key; a 512-grid ragged batch of 33..1025 points a
-    // side: 13.8 ms with 4 columns per lane and >= 64 rows, 11.7 ms with 2 and
-    // >= 32; 15.4 ms with the table's chunks).
+    // over several grids plans of 4 or more grids use batch_rows, and every
+    // plan of 2 or more grids 2 columns per lane (one launch per key; a
+    // 512-grid ragged batch of 33..1025 points a side: 13.8 ms with 4 columns
+    // per lane and >= 64 rows, 11.7 ms with 2 and >= 32; 15.4 ms with the
+    // table's chunks).
     const bool tile_op = (op.kind == OP_SWEEP || op.kind == OP_RESTRICT) && !(op.flags & SW_NORM);
     if (tile_op && nplan >= kBatchManyGrids) {
-        const bool four = (op.flags & SW_FOUR) != 0;
-        t = make_tiling(L.m, L.n, kBatchV, std::max(t.ty, four ? kBatchFourMinRows : kBatchMinRows), 0, t.H);
+        const int hi = (op.flags & SW_FOUR) ? kBatchFourMaxRows : kBatchRows[1];
+        t = make_tiling(L.m, L.n, kBatchV, std::max(t.ty, batch_rows(nodes, 2, kBatchRows[0], hi)), 0, t.H);
     } else if (tile_op && nplan >= 2) {
         t = make_tiling(L.m, L.n, kBatchV, t.ty, 0, t.H);
     }
@@ -3142,8 +3151,10 @@ lap_status get_plan(lap_ctx* c, const std::vector<lap_grid*>& gs, const std::vec
         // only (one kernel for all three ran at the V = 4 variant's occupancy)
         using GoIt = std::pair<std::pair<lap_grid*, Op>, BatchItem>;
         std::map<std::tuple<int, int, int, int>, std::vector<GoIt>> sub;
+        double nodes = 0.0;
+        for (const auto& go : v) nodes += nint(go.first->geo[go.second.level]);
         for (auto& go : v) {
-            const BatchItem it = make_item(go.first, go.second, o, gs.size());
+            const BatchItem it = make_item(go.first, go.second, o, gs.size(), nodes);
             const int bk = batch_kind(go.second);
             const int vkey = bk == BK_FUSED ? it.V : 0;
             // the merged residual-norm and defect kernels are built for the canonical V only
