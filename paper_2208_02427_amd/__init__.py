@@ -51,11 +51,17 @@ def _ptr(t):
     return ctypes.c_void_p(0 if t is None else t.data_ptr())
 
 
+_torch_gpu = None   # torch, once it has said that it has a GPU (asking takes microseconds, every call asked thrice)
+
+
 def _torch():
-    import torch
-    if not torch.cuda.is_available():
-        raise RuntimeError("liblap needs a ROCm GPU (torch.cuda.is_available() is False)")
-    return torch
+    global _torch_gpu
+    if _torch_gpu is None:
+        import torch
+        if not torch.cuda.is_available():
+            raise RuntimeError("liblap needs a ROCm GPU (torch.cuda.is_available() is False)")
+        _torch_gpu = torch
+    return _torch_gpu
 
 
 SMOOTHERS = {"rb": LAP_SMOOTH_RB, "zebra": LAP_SMOOTH_ZEBRA}
@@ -94,6 +100,8 @@ class Context:
         self.device = torch.device(device)
         self.arena = torch.empty(int(arena_bytes), dtype=torch.uint8, device=self.device)
         self.stream = torch.cuda.Stream(device=self.device)
+        # recorded anew at every entry / exit: a wait refers to the record before it
+        self._entered, self._left = torch.cuda.Event(), torch.cuda.Event()
         h = ctypes.c_void_p()
         _check(lib().lap_ctx_create(_ptr(self.arena), int(arena_bytes), ctypes.c_void_p(self.stream.cuda_stream),
                                     ctypes.byref(h)))
@@ -108,12 +116,12 @@ class Context:
 
     # stream ordering around library calls
     def _enter(self):
-        torch = _torch()
-        self.stream.wait_stream(torch.cuda.current_stream(self.device))
+        self._entered.record(_torch().cuda.current_stream(self.device))
+        self.stream.wait_event(self._entered)
 
     def _leave(self):
-        torch = _torch()
-        torch.cuda.current_stream(self.device).wait_stream(self.stream)
+        self._left.record(self.stream)
+        _torch().cuda.current_stream(self.device).wait_event(self._left)
 
     def close(self):
         if getattr(self, "handle", None):
