@@ -106,7 +106,10 @@ static hipError_t launch_batch_fused_v(int fl, const BatchItem* items, const int
                     default: return hipErrorInvalidValue;
                 }
             } else {
-                return hipErrorInvalidValue;
+                switch (fl) {
+                    LAP_CASE(SW_FOUR)   // four sweeps of red-black SOR
+                    default: return hipErrorInvalidValue;
+                }
             }
 #undef LAP_CASE
     }

@@ -44,6 +44,8 @@ __global__ __launch_bounds__(kBlock) void k_fused(SweepArgs<T> A) {
     X(SW_PROBE | SW_RESTRICT | SW_TWO | SW_NORM) X(SW_PROBE | SW_RESTRICT | SW_TWO | SW_NORM | SW_F)  \
     X(SW_PROBE | SW_RESTRICT | SW_NORM) X(SW_PROBE | SW_RESTRICT | SW_NORM | SW_F)                \
     X(SW_PROBE | SW_TWO | SW_NORM) X(SW_PROBE | SW_TWO | SW_NORM | SW_F)
+// FP64 only: four sweeps of red-black SOR
+#define LAP_FUSED_FLAGS64(X) X(SW_FOUR) X(SW_FOUR | SW_F)
 // FP32 only: the mixed loop's post-smoothing + defect pass and the passes of
 // a step's cycles after the first
 // (post + defect only with the two columns per lane of its fixed tiling)
@@ -70,7 +72,10 @@ hipError_t launch_fused_v(const SweepArgs<T>& a, int flags, hipStream_t s) {
                     default: return hipErrorInvalidValue;
                 }
             } else {
-                return hipErrorInvalidValue;
+                switch (flags) {
+                    LAP_FUSED_FLAGS64(LAP_CASE)
+                    default: return hipErrorInvalidValue;
+                }
             }
 #undef LAP_CASE
     }

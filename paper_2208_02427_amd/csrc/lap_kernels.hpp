@@ -188,7 +188,7 @@ enum : int {
                      // cycle that continues from a correction)
     SW_FOUR = 1024,  // fused pass: four sweeps (a cycle's two post-smoothing sweeps after its bilinear
                      // correction, then the next cycle's two pre-smoothing sweeps, residual and full
-                     // weighting: SW_PROLONG | SW_RESTRICT)
+                     // weighting: SW_PROLONG | SW_RESTRICT); alone, four sweeps of red-black SOR
     SW_UNUSED = 1 << 30,  // stands for a flag set a build of the kernels leaves out
 };
 

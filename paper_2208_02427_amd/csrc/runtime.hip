@@ -913,16 +913,29 @@ PassPlan pass_plan(const lap_ctx* c, const lap_opts& o, bool keep_parity) {
     return p;
 }
 
-// Sweeps per pass of one red-black SOR check block of `ce` sweeps: pairs
-// with fusion (an odd count ends with a single sweep), else single sweeps.
+// Sweeps per pass of one red-black SOR check block of `ce` sweeps. With
+// fusion: two in the first pass, which also carries the norms (their partial
+// sums belong to the two-sweep tiling), then fours, whose field and source
+// cross memory once per four sweeps, then what is left. A large four-sweep
+// pass costs what a two-sweep pass does (8193^2 544 us either way: both wait
+// for memory), so 200 sweeps of 3000 x 2201 in blocks of 50 went from 2945 to
+// 1766 us; on small grids a pass is the instructions of one wave (129^2: 17.4 us
+// against 9.6 us) and the gain is a tenth. Without fusion: single sweeps.
 std::vector<int> sor_passes(const lap_ctx* c, int ce) {
     std::vector<int> p;
     if (!c->fuse) {
         p.assign(ce, 1);
         return p;
     }
-    p.assign(ce / 2, 2);
-    if (ce % 2) p.push_back(1);
+    // the first pass carries the norms on their canonical tiling: two sweeps
+    int k = ce;
+    if (k >= 2) {
+        p.push_back(2);
+        k -= 2;
+    }
+    for (; k >= 4; k -= 4) p.push_back(4);
+    if (k >= 2) p.push_back(2);
+    if (k % 2) p.push_back(1);
     return p;
 }
 
@@ -1958,7 +1971,7 @@ void plan_step(lap_grid* g, const lap_opts& o, int s, int part, std::vector<Op>&
                     cur = 1 - cur;
                     continue;
                 }
-                const int fl = fb | (k == 0 ? SW_NORM : 0) | (pp[k] == 2 ? SW_TWO : 0);
+                const int fl = fb | (k == 0 ? SW_NORM : 0) | (pp[k] == 2 ? SW_TWO : pp[k] == 4 ? SW_FOUR : 0);
                 push_op<double>(ops, key_pre(0, 0) + 2L * k, OP_SWEEP, 0, fl, g->psi[cur], g->psi[1 - cur], g->f64,
                                 nullptr, nullptr, o.omega);
                 if (k == 0)
@@ -3763,10 +3776,11 @@ extern "C" lap_status lap_autotune(lap_ctx* c, int32_t m, int32_t n, int32_t rep
     // the variant each class is timed on: pre-smoothing from zero with the
     // restriction (coarse levels, FP32 level 0), post-smoothing with the
     // prolongation (with and without a right-hand side, as the one-sweep kernel)
-    auto base_flags = [](int cls) {
+    auto base_flags = [](int cls, int dt) {
         if (cls == KC_PRE) return (int)(SW_RESTRICT | SW_TWO | SW_ZERO);
         if (cls == KC_TWO) return (int)(SW_TWO | SW_PROLONG);
         if (cls == KC_TWO_PLAIN) return (int)SW_TWO;
+        if (cls == KC_FOUR && dt == 0) return (int)SW_FOUR;   // red-black SOR
         if (cls == KC_FOUR) return (int)(SW_FOUR | SW_PROLONG | SW_RESTRICT | SW_RDIFF);
         return 0;
     };
@@ -3776,19 +3790,19 @@ extern "C" lap_status lap_autotune(lap_ctx* c, int32_t m, int32_t n, int32_t rep
                     (int)KC_PRE, (int)KC_TWO, (int)KC_TWO_PLAIN, (int)KC_FOUR}) {
         for (int dt = 0; dt < 2; ++dt) {
             if ((cls == KC_DEFECT || cls == KC_TWO_PLAIN) && dt == 1) continue;   // FP64 only
-            if (cls == KC_FOUR && dt == 0) continue;                              // FP32 only
             double best = 1e30;
             Cand bc{2, 0, c->wave_cap};
             for (const Cand& cd : cands) {
                 const int H = (cls == KC_PRE || cls == KC_TWO || cls == KC_TWO_PLAIN || cls == KC_FOUR)
-                                  ? fused_halo(base_flags(cls))
+                                  ? fused_halo(base_flags(cls, dt))
                                   : 2;
                 const Tiling t = make_tiling(m, n, cd.V, cd.ty, cd.tgt, lane_halo(H, cd.V));
                 double total = 0.0;
                 for (int fl0 : {0, (int)SW_F}) {
-                    if (fl0 == 0 && cls != KC_SWEEP && cls != KC_TWO && cls != KC_TWO_PLAIN) continue;
-                    if (fl0 == 0 && (cls == KC_PRE || cls == KC_FOUR)) continue;
-                    const int fl = fl0 | base_flags(cls);
+                    if (fl0 == 0 && cls != KC_SWEEP && cls != KC_TWO && cls != KC_TWO_PLAIN &&
+                        !(cls == KC_FOUR && dt == 0))
+                        continue;
+                    const int fl = fl0 | base_flags(cls, dt);
                     auto go = [&]() {
                         return dt == 0 ? tune_launch<double>(c, cls, t, m, n, P, Pc, B, fl)
                                        : tune_launch<float>(c, cls, t, m, n, P, Pc, B, fl);

@@ -249,3 +249,25 @@ def test_mixed_norms_alone_equal_batched():
         assert np.array_equal(g.read().cpu().numpy(), ub)
         g.destroy()
     ctx2.close()
+
+
+@pytest.mark.parametrize("m,n,ce,source", [(33, 33, 6, True), (300, 211, 7, False), (1026, 259, 50, True),
+                                           (515, 1200, 9, False), (129, 40, 4, True)])
+def test_sor_four_sweep_passes_bitwise(m, n, ce, source):
+    """Check blocks long enough for four-sweep passes (remainders of 0-3
+    sweeps behind them, several windows and chunks, even heights that walk all
+    chunks downwards) against one launch per sweep: field, counts and norms."""
+    torch, lap = need_gpu()
+    psi, f, dx, dy = rand_problem(m, n, seed=m + n, dx=1.0 / (m - 1), dy=1.2 / (m - 1), source=source)
+    say("sor four", m, n, ce, source)
+    out = []
+    for fuse in (False, True):
+        ctx = lap.Context(arena_bytes=256 << 20)
+        ctx.set_fusion(fuse)
+        g = ctx.grid(to_dev(torch, psi), to_dev(torch, f) if source else None, dx, dy, alloc=lap.LAP_ALLOC_ADI)
+        info = g.solve("sor", omega=1.7, tol=0.0, max_iter=3 * ce, check_every=ce)
+        out.append((info["iterations"], g.read().cpu().numpy()))
+        g.destroy()
+        ctx.close()
+    assert out[0][0] == out[1][0] == 3 * ce
+    assert np.array_equal(out[0][1], out[1][1])
