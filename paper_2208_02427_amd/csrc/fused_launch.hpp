@@ -44,8 +44,12 @@ __global__ __launch_bounds__(kBlock) void k_fused(SweepArgs<T> A) {
     X(SW_PROBE | SW_RESTRICT | SW_TWO | SW_NORM) X(SW_PROBE | SW_RESTRICT | SW_TWO | SW_NORM | SW_F)  \
     X(SW_PROBE | SW_RESTRICT | SW_NORM) X(SW_PROBE | SW_RESTRICT | SW_NORM | SW_F)                \
     X(SW_PROBE | SW_TWO | SW_NORM) X(SW_PROBE | SW_TWO | SW_NORM | SW_F)
-// FP64 only: four sweeps of red-black SOR
-#define LAP_FUSED_FLAGS64(X) X(SW_FOUR) X(SW_FOUR | SW_F)
+// FP64 only: four sweeps of red-black SOR, and a cycle's post-smoothing with
+// the next one's pre-smoothing (on the norms' tiling: two columns per lane)
+#define LAP_FUSED_FLAGS64(X)                                                                       \
+    X(SW_FOUR) X(SW_FOUR | SW_F)                                                                   \
+    X(V == 2 ? SW_FOUR | SW_PROLONG | SW_NORM | SW_RESTRICT : SW_UNUSED)                           \
+    X(V == 2 ? SW_FOUR | SW_PROLONG | SW_NORM | SW_RESTRICT | SW_F : SW_UNUSED | SW_F)
 // FP32 only: the mixed loop's post-smoothing + defect pass and the passes of
 // a step's cycles after the first
 // (post + defect only with the two columns per lane of its fixed tiling)
@@ -59,7 +63,7 @@ hipError_t launch_fused_v(const SweepArgs<T>& a, int flags, hipStream_t s) {
     switch (flags) {
 #define LAP_CASE(F)                                      \
     case (F):                                            \
-        if constexpr ((F) == SW_UNUSED)                  \
+        if constexpr (((F) & SW_UNUSED) != 0)            \
             return hipErrorInvalidValue;                 \
         else                                             \
             k_fused<T, V, (F)><<<grid, block, 0, s>>>(a);\

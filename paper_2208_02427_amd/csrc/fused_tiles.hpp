@@ -82,10 +82,11 @@ constexpr int fused_sweeps() {
 // stages' own are in flight: six for two FP64 sweeps with the restriction,
 // seven without, two less where a right-hand side streams along or FP64 rows
 // do besides FP32 ones (their registers cost a wavefront of occupancy);
-// four columns a lane keep two in flight.
+// four columns a lane and four sweeps with norms and a right-hand side (225
+// registers; 268 with 14 rows, one wavefront a SIMD) keep two in flight.
 template <typename T, int V, int FL>
 constexpr int fused_ring() {
-    if (fused_sweeps<FL>() == 4) return 14;
+    if (fused_sweeps<FL>() == 4) return (FL & SW_NORM) && (FL & SW_F) ? 12 : 14;
     if (fused_sweeps<FL>() == 1 || V == 4) return 8;
     return (FL & SW_DEF) || (sizeof(T) == 8 && (FL & SW_F)) ? 10 : 12;
 }
@@ -104,6 +105,7 @@ struct FusedRegs {
     T u[K][V], f[(FL & SW_F) ? K : 1][V];
     T c[(FL & SW_PROLONG) ? KC : 1][VC];
     T rodd[V], wodd, eodd, reven[V];                       // residual rows behind the last one
+    T mid[(FL & SW_NORM) && NS == 4 ? V : 1];              // a row of the iterate after two of four sweeps
     double psi[(FL & SW_DEF) ? KD : 1][V], g[(FL & SW_DEF) ? KD : 1][V];
     double s2, mx;
 };
@@ -167,6 +169,22 @@ __device__ __forceinline__ void colour_row(T (&c)[V], const T (&S)[V], const T (
     }
 }
 
+// Adds the residual of a row (c, between rows S and N) to the lane's norms.
+template <typename T, int V, int FL>
+__device__ __forceinline__ void norm_row(const SweepArgs<T>& A, FusedRegs<T, V, FL>& R, const FusedLane<T, V>& l,
+                                         const T (&S)[V], const T (&c)[V], const T (&N)[V], const T (&f)[V]) {
+    const T W0 = lane_prev(c[V - 1]), E0 = lane_next(c[0]);
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+        const T W = e > 0 ? c[e - 1] : W0;
+        const T E = e < V - 1 ? c[e + 1] : E0;
+        const T L = fma(-A.d, c[e], fma(A.cy, S[e] + N[e], A.cx * (W + E)));
+        const double r = l.cout[e] ? (double)((FL & SW_F) ? f[e] - L : T(0) - L) : 0.0;
+        R.s2 = fma(r, r, R.s2);
+        R.mx = fmax(R.mx, fabs(r));
+    }
+}
+
 // Step of phase PH at row j: input row j + 1 enters, stage s updates rows
 // j - 2s and j - 2s - 1, row q = j + 1 - 2 NS is final.
 template <typename T, int V, int FL, bool EDGE, bool NT, int PH>
@@ -199,28 +217,26 @@ __device__ __forceinline__ void fused_step(const SweepArgs<T>& A, FusedRegs<T, V
             }
         }
     }
-    if constexpr ((FL & SW_NORM) != 0) {
+    if constexpr ((FL & SW_NORM) != 0 && NS < 4) {
         // residual of the input at row j + 1, before row j changes
-        const T(&c)[V] = in;
-        const T(&S)[V] = R.u[ring_slot<K>(PH, 0)];
-        const T(&N)[V] = R.u[ring_slot<K>(PH, 2)];
-        const T(&f)[V] = R.f[HASF ? ring_slot<FK>(PH, 1) : 0];
-        if (j + 1 >= j0 && j + 1 <= j1) {
-            const T W0 = lane_prev(c[V - 1]), E0 = lane_next(c[0]);
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-                const T W = e > 0 ? c[e - 1] : W0;
-                const T E = e < V - 1 ? c[e + 1] : E0;
-                const T L = fma(-A.d, c[e], fma(cy, S[e] + N[e], cx * (W + E)));
-                const double r = l.cout[e] ? (double)(HASF ? f[e] - L : T(0) - L) : 0.0;
-                R.s2 = fma(r, r, R.s2);
-                R.mx = fmax(R.mx, fabs(r));
-            }
-        }
+        if (j + 1 >= j0 && j + 1 <= j1)
+            norm_row<T, V, FL>(A, R, l, R.u[ring_slot<K>(PH, 0)], in, R.u[ring_slot<K>(PH, 2)],
+                               R.f[HASF ? ring_slot<FK>(PH, 1) : 0]);
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int r = j - 2 * s;
+        if constexpr ((FL & SW_NORM) != 0 && NS == 4) {
+            // between the second and the third sweep: residual at row j - 4 of the
+            // iterate after two (row j - 5's first colour changed a step ago)
+            if (s == 2) {
+                const T(&c)[V] = R.u[ring_slot<K>(PH, -4)];
+                if (r >= j0 && r <= j1)
+                    norm_row<T, V, FL>(A, R, l, R.mid, c, R.u[ring_slot<K>(PH, -3)],
+                                       R.f[HASF ? ring_slot<FK>(PH, -4) : 0]);
+                copy<T, V>(R.mid, c);
+            }
+        }
         if (!EDGE || (r >= 1 && r <= A.n - 2))
             colour_row<T, V, JP, HASF>(R.u[ring_slot<K>(PH, -2 * s)], R.u[ring_slot<K>(PH, -2 * s - 1)],
                                        R.u[ring_slot<K>(PH, -2 * s + 1)],
@@ -528,6 +544,7 @@ __device__ __forceinline__ void fused_tile(const SweepArgs<T>& A0, int tile, int
             zero<T, V>(R.reven);
             R.wodd = R.eodd = T(0);
         }
+        if constexpr ((FL & SW_NORM) != 0 && NS == 4) zero<T, V>(R.mid);
         // whole turns of the ring without an exit (one from inside a turn would
         // have the compiler wait for every load at the head of the loop), then
         // the rest, whose copy of the steps serves both kinds of chunks

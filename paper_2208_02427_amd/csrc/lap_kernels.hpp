@@ -51,6 +51,20 @@ constexpr int kNormH = 6;
 // buy parallelism, up to a point.  Below ~6000 rows the 16-row minimum
 // decides instead.
 constexpr int kNormWaves = 32768;
+// Grids from kMergedNodes interior nodes on run one pass per cycle over the
+// finest level (merged_ok), whose norms, like those of every other kernel that
+// forms them, belong to this tiling: a halo for four sweeps and the
+// restriction, and as many waves as are resident at once with that pass's
+// registers (two a SIMD).  20 FP64 cycles of 8193^2, without / with a source: 2048
+// waves 11.84 / 14.15 ms, 3072 12.50 / 14.79, 6144 11.92 / 14.29; of 4097^2
+// 4.41 / 5.10, 4.55 / 5.39, 4.53 / 5.27 ms.  The line: one pass against two
+// per cycle 2049^2 2.47 against 2.76 ms, 1537^2 2.17 against 2.35, but 1025^2
+// 1.72 against 1.73 and 513^2 1.42 against 1.40, where a pass is its waves'
+// instructions and not memory.
+constexpr int64_t kMergedNodes = (int64_t)1 << 21;
+constexpr int kMergedH = 10;
+constexpr int kMergedWaves = 2048;
+inline bool merged_size(int m, int n) { return (int64_t)(m - 2) * (n - 2) >= kMergedNodes; }
 
 // Tiling of an m x n level with V columns per lane.  ty > 0: chunks of ty
 // rows.  ty == 0: size the chunks so the launch has about `target` waves
@@ -128,6 +142,7 @@ inline Tiling norm_tiling(int m, int n, int kind = NORM_PASS) {
     if (kind == NORM_DEFECT)
         return make_tiling(m, n, kNormDefectV, 0, 16384, 2, n <= kDefectShortRowsN ? 16 : kDefectMinRows);
     if (kind == NORM_POSTDEF) return make_tiling(m, n, 2, 0, 16384, kNormH, n > kPostDefShortRowsN ? 16 : 64);
+    if (merged_size(m, n)) return make_tiling(m, n, kNormPassV, 0, kMergedWaves, kMergedH);
     return make_tiling(m, n, kNormPassV, 0, kNormWaves, kNormH);
 }
 // Blocks of rows a chunk of the post-smoothing + defect pass may hold.

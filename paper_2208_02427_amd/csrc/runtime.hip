@@ -415,6 +415,17 @@ namespace {
 void plans_clear(lap_ctx* c);   // batch plans (defined with the batch executor)
 }
 
+// State of an FP64 multigrid solve with one finest pass per cycle (merged_ok).
+struct MergedRun {
+    bool on = false;
+    int cur = 0;                     // buffer of psi that the next step reads:
+    bool pre = false;                // pre-smoothed, to be corrected by ec and post-smoothed, or an iterate
+    const double* ec = nullptr;
+    // per step, where the iterate its test saw is: its buffer, or that buffer + 2 if it has to be
+    // formed there from the other buffer and ec
+    std::vector<uint8_t> log;
+};
+
 // ========================================================================= grid
 struct lap_grid {
     lap_ctx* ctx = nullptr;
@@ -462,8 +473,10 @@ struct lap_grid {
     bool zebra_ok = false;
     bool pdef = false;               // the running mixed solve uses the post-smoothing + defect pass
     lap_opts batch_opts{};
+    MergedRun mr;                    // the running solve, if it takes one finest pass per cycle
     // graph cache
     hipGraphExec_t graph = nullptr;
+    hipGraphExec_t graph_odd = nullptr;    // one pass per cycle: the step from psi[1] (graph: from psi[0])
     std::string graph_key;
     std::vector<std::string> graph_seen;   // options of recent solves (a repeat captures the graph)
     std::string graph_run_key;             // options of the running solve
@@ -1825,23 +1838,112 @@ int max_steps(const lap_opts& o) {
     }
 }
 
-hipError_t capture(lap_grid* g, const char* key, const std::function<hipError_t()>& body) {
+// Whether an FP64 multigrid solve of g takes one pass per cycle over the
+// finest level: the last cycle's correction and post-smoothing, the norms of
+// its result, and the next cycle's pre-smoothing, residual and full
+// weighting.  Two passes move 4.5 values a node (6.5 with a source), one 2.5
+// (3.5), and large passes are bound by HBM: 8193^2 to 1e-10 6.14 -> 4.35 ms,
+// 4097^2 2.13 -> 1.66 ms.  The price is that the tested iterate is never
+// stored: a solve that stops forms it again by one plain pass, unless the
+// tests predicted the stop (then the iterate is formed and tested alone first).
+bool merged_ok(const lap_grid* g, const lap_opts& o) {
+    return o.method == LAP_MG && o.precision == LAP_FP64 && o.smoother == LAP_SMOOTH_RB && !o.fmg && o.nu1 == 2 &&
+           o.nu2 == 2 && g->ctx->fuse && g->geo.size() >= 2 && merged_size(g->m, g->n);
+}
+
+// One cycle of such a solve, from its finest pass (reading psi[cur], writing
+// the other buffer) down to the correction of the first coarse level, whose
+// buffer is returned: `pre` takes the merged pass, else psi[cur] is an
+// iterate and the pass only pre-smooths.  The finalisation in it is the
+// stopping test.
+const double* plan_merged(lap_grid* g, const lap_opts& o, int cur, bool pre, std::vector<Op>& ops) {
+    HierView<double> H = view64(g, o.nu1);
+    const int fb = g->f64 ? SW_F : 0;
+    const int ri = g->geo.size() == 2 ? 0 : vcycle_result_index(g->ctx, o);
+    const double* ec = ri == 0 ? H.u0[1] : H.u1[1];
+    const int fl = fb | SW_NORM | SW_RESTRICT | (pre ? SW_FOUR | SW_PROLONG : SW_TWO);
+    push_op<double>(ops, key_pre(0, 0), OP_SWEEP, 0, fl, g->psi[cur], g->psi[1 - cur], g->f64, pre ? ec : nullptr,
+                    H.b[1], o.omega);
+    push_op<double>(ops, key_norm_fin(0), OP_FINALIZE, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0);
+    const int cres = plan_vcycle<double>(g, H, 1, o, false, PART_ALL, ops);
+    return cres == 0 ? H.u0[1] : H.u1[1];
+}
+
+// psi[cur] corrected and post-smoothed into the other buffer.
+Op merged_post(lap_grid* g, const lap_opts& o, int cur) {
+    std::vector<Op> ops;
+    push_op<double>(ops, key_post(0, 0), OP_SWEEP, 0, SW_PROLONG | SW_TWO | (g->f64 ? SW_F : 0), g->psi[cur],
+                    g->psi[1 - cur], g->f64, g->mr.ec, nullptr, o.omega);
+    return ops[0];
+}
+
+// The test of the iterate alone, as step s opens with it (forming the
+// iterate first): mode 0 records it, 2 only if it ends the solve.
+hipError_t merged_test(lap_grid* g, const lap_opts& o, int s, int mode) {
+    MergedRun& r = g->mr;
+    std::vector<Op> ops;
+    if (r.pre) {
+        ops.push_back(merged_post(g, o, r.cur));
+        r.cur = 1 - r.cur;
+        r.pre = false;
+    }
+    push_op<double>(ops, key_pre(0, 0), OP_SWEEP, 0, SW_PROBE | SW_NORM | SW_RESTRICT | SW_TWO | (g->f64 ? SW_F : 0),
+                    g->psi[r.cur], nullptr, g->f64, nullptr, nullptr, o.omega);
+    push_op<double>(ops, key_norm_fin(0), OP_FINALIZE, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0,
+                    mode == 2 ? kProbeFinalize : 0);
+    r.log.resize(s + 1);
+    r.log[s] = (uint8_t)r.cur;
+    return exec_ops(g, ops);
+}
+
+// Step s: test and cycle.
+hipError_t merged_step(lap_grid* g, const lap_opts& o, int s) {
+    MergedRun& r = g->mr;
+    const bool pre = r.pre;
+    const int from = r.cur;
+    r.log.resize(s + 1);
+    r.log[s] = (uint8_t)(pre ? 2 + (1 - from) : from);
+    r.cur = 1 - from;
+    r.pre = true;
+    if (pre && g->graph_on) return hipGraphLaunch(from == 0 ? g->graph : g->graph_odd, g->ctx->stream);
+    std::vector<Op> ops;
+    r.ec = plan_merged(g, o, from, pre, ops);
+    return exec_ops(g, ops);
+}
+
+void drop_graphs(lap_grid* g) {
+    if (g->graph) (void)hipGraphExecDestroy(g->graph);
+    if (g->graph_odd) (void)hipGraphExecDestroy(g->graph_odd);
+    g->graph = g->graph_odd = nullptr;
+    g->graph_key.clear();
+}
+
+hipError_t capture(lap_grid* g, const char* key, const std::function<hipError_t()>& body,
+                   const std::function<hipError_t()>* odd = nullptr) {
     lap_ctx* c = g->ctx;
     if (g->graph != nullptr && g->graph_key == key) return hipSuccess;
-    if (g->graph) {
-        HIPERR(hipGraphExecDestroy(g->graph));
-        g->graph = nullptr;
+    drop_graphs(g);
+    const auto one = [&](hipGraphExec_t* out, const std::function<hipError_t()>& fn) -> hipError_t {
+        HIPERR(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
+        hipError_t e = fn();
+        hipGraph_t tmp = nullptr;
+        hipError_t e2 = hipStreamEndCapture(c->stream, &tmp);
+        if (e != hipSuccess) return e;
+        if (e2 != hipSuccess) return e2;
+        e = hipGraphInstantiate(out, tmp, nullptr, nullptr, 0);
+        hipGraphDestroy(tmp);
+        return e;
+    };
+    HIPERR(one(&g->graph, body));
+    if (odd != nullptr) {
+        const hipError_t e = one(&g->graph_odd, *odd);
+        if (e != hipSuccess) {
+            drop_graphs(g);
+            return e;
+        }
     }
-    HIPERR(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    hipError_t e = body();
-    hipGraph_t tmp = nullptr;
-    hipError_t e2 = hipStreamEndCapture(c->stream, &tmp);
-    if (e != hipSuccess) return e;
-    if (e2 != hipSuccess) return e2;
-    e = hipGraphInstantiate(&g->graph, tmp, nullptr, nullptr, 0);
-    hipGraphDestroy(tmp);
-    if (e == hipSuccess) g->graph_key = key;
-    return e;
+    g->graph_key = key;
+    return hipSuccess;
 }
 
 bool use_graph(lap_grid* g, const lap_opts& o) {
@@ -1862,6 +1964,8 @@ lap_status prepare(lap_grid* g, const lap_opts& o, bool init = true) {
         if (st != LAP_OK) return st;
     }
     g->step_idx = 0;
+    g->mr = MergedRun{};
+    g->mr.on = init && merged_ok(g, o);   // a batch runs its own plans
     g->pdef = postdef_ok(g, o);   // fixed for the whole solve
     g->e_idx = vcycle_result_index(g->ctx, o);
     if (o.method == LAP_MG && o.precision == LAP_MIXED && o.inner > 1 && !g->l32.empty()) {
@@ -1898,7 +2002,8 @@ lap_status prepare(lap_grid* g, const lap_opts& o, bool init = true) {
     if (use_graph(g, o)) {
         char key[128];
         if (o.precision == LAP_FP64)
-            snprintf(key, sizeof key, "mg64:%d:%d:%d:%.17g", o.smoother, o.nu1, o.nu2, o.omega);
+            snprintf(key, sizeof key, "mg64%s:%d:%d:%d:%.17g", g->mr.on ? "+m" : "", o.smoother, o.nu1, o.nu2,
+                     o.omega);
         else
             snprintf(key, sizeof key, "mixed%s:%d:%d:%d:%d:%.17g", g->pdef ? "+pd" : "", o.smoother, o.nu1, o.nu2,
                      o.inner, o.omega);
@@ -1915,7 +2020,18 @@ lap_status prepare(lap_grid* g, const lap_opts& o, bool init = true) {
     if (g->graph_on) {
         const std::string key = g->graph_run_key;
         hipError_t e;
-        if (o.precision == LAP_FP64) {
+        if (g->mr.on) {
+            const std::function<hipError_t()> odd = [&]() {
+                std::vector<Op> ops;
+                g->mr.ec = plan_merged(g, o, 1, true, ops);
+                return exec_ops(g, ops);
+            };
+            e = capture(g, key.c_str(), [&]() {
+                std::vector<Op> ops;
+                g->mr.ec = plan_merged(g, o, 0, true, ops);
+                return exec_ops(g, ops);
+            }, &odd);
+        } else if (o.precision == LAP_FP64) {
             e = capture(g, key.c_str(), [&]() {
                 HierView<double> H = view64(g, o.nu1);
                 std::vector<Op> ops;
@@ -2002,6 +2118,7 @@ void plan_step(lap_grid* g, const lap_opts& o, int s, int part, std::vector<Op>&
 hipError_t step(lap_grid* g, const lap_opts& o, int part = PART_ALL) {
     const int s = g->step_idx;
     if (part != PART_HEAD) g->step_idx++;
+    if (g->mr.on) return part == PART_HEAD ? merged_test(g, o, s, 0) : merged_step(g, o, s);
     lap_ctx* c = g->ctx;
     const bool graph = g->graph_on && part == PART_ALL && !(o.fmg && s == 0);
     if (graph && o.method == LAP_MG) {
@@ -2049,7 +2166,17 @@ int result_buffer(lap_grid* g, const lap_opts& o, const Ctrl& h) {
 lap_status fixup(lap_grid* g, const lap_opts& o, const Ctrl& h) {
     lap_ctx* c = g->ctx;
     const size_t bytes = (size_t)g->n * g->P * 8;
-    if (result_buffer(g, o, h) == 1)
+    int rb = result_buffer(g, o, h);
+    if (g->mr.on) {
+        const uint8_t at = h.checks > 0 ? g->mr.log[h.checks - 1] : 0;
+        rb = at & 1;
+        if (at & 2) {
+            // the pass that tested the iterate went on to the next cycle: form it again
+            HIPCHK(launch_ctrl_init(g->ctrl, o.tol, o.stop, o.max_iter, 1, c->stream));
+            HIPCHK(exec_op(g, merged_post(g, o, 1 - rb)));
+        }
+    }
+    if (rb == 1)
         HIPCHK(hipMemcpyAsync(g->psi[0], g->psi[1], bytes, hipMemcpyDeviceToDevice, c->stream));
     if (o.method == LAP_ADI) g->psi1_stale = true;   // copied when a two-buffer method next starts
     return LAP_OK;
@@ -2167,6 +2294,10 @@ lap_status solve_one(lap_grid* g, const lap_opts& o, lap_info* info) {
     c->rec_solve = c->timing ? c->solve_serial++ : -1;
     Ctrl h{};
     const std::function<hipError_t(int, bool*)> probe = [&](int s, bool* did) -> hipError_t {
+        if (g->mr.on) {
+            *did = true;
+            return merged_test(g, o, s, 2);
+        }
         const std::vector<Op> ops = probe_ops(g, o, s);
         *did = !ops.empty();
         return ops.empty() ? hipSuccess : exec_ops(g, ops);
@@ -2495,7 +2626,7 @@ lap_status lap_grid_destroy(lap_grid* g) {
     lap_ctx* c = g->ctx;
     hipStreamSynchronize(c->stream);
     plans_clear(c);   // cached batch plans may point into this grid
-    if (g->graph) hipGraphExecDestroy(g->graph);
+    drop_graphs(g);
     for (void* p : g->allocs) c->arena.release(p);
     auto it = std::find(c->grids.begin(), c->grids.end(), g);
     if (it != c->grids.end()) c->grids.erase(it);
@@ -2907,11 +3038,7 @@ void plans_clear(lap_ctx* c) {
 void invalidate_cached(lap_ctx* c) {
     plans_clear(c);
     for (lap_grid* g : c->grids)
-        if (g->graph) {
-            hipGraphExecDestroy(g->graph);
-            g->graph = nullptr;
-            g->graph_key.clear();
-        }
+        drop_graphs(g);
 }
 
 int batch_kind(const Op& op) {

@@ -271,3 +271,40 @@ def test_sor_four_sweep_passes_bitwise(m, n, ce, source):
         ctx.close()
     assert out[0][0] == out[1][0] == 3 * ce
     assert np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("m,n,source", [(2561, 2049, True), (1537, 2049, False), (2401, 2001, True)])
+def test_one_finest_pass_per_cycle_bitwise(m, n, source):
+    """Grids of 2^21 interior nodes and more merge a cycle's post-smoothing
+    with the next cycle's pre-smoothing: every way a solve may end (the
+    tested iterate formed again into either buffer, a test alone, max_iter,
+    converged on arrival), and solves that follow one another on one grid
+    (captured graphs), bitwise as with one launch per sweep."""
+    torch, lap = need_gpu()
+    psi, f, dx, dy = rand_problem(m, n, seed=m, dx=1.0 / (m - 1), dy=1.1 / (m - 1), source=source)
+    runs = [dict(tol=0.0, max_iter=3), dict(tol=0.0, max_iter=4), dict(tol=0.5, max_iter=9),
+            dict(tol=2e-2, max_iter=9), dict(tol=2e-3, max_iter=9), dict(tol=2e-4, max_iter=9),
+            dict(tol=1e-9, max_iter=30), dict(tol=1e-9, max_iter=30, stop="res_inf"), dict(tol=1e-8, max_iter=0)]
+    out = []
+    for fuse in (False, True):
+        ctx = lap.Context(arena_bytes=2 << 30)
+        ctx.set_fusion(fuse)
+        dpsi = to_dev(torch, psi)
+        g = ctx.grid(dpsi, to_dev(torch, f) if source else None, dx, dy, alloc=lap.LAP_ALLOC_FP64)
+        got = []
+        for kw in runs:
+            say("one pass", m, n, source, fuse, kw)
+            g.write(dpsi)
+            info = g.solve("mg", **kw)
+            got.append((info["iterations"], info["rel_res_l2"], info["res_linf"], g.read().cpu().numpy()))
+        # on from where the last solve stopped: a test of that iterate, then cycles
+        g.solve("mg", tol=1e-3, max_iter=9)
+        info = g.solve("mg", tol=1e-3, max_iter=2)
+        got.append((info["iterations"], info["rel_res_l2"], info["res_linf"], g.read().cpu().numpy()))
+        out.append(got)
+        g.destroy()
+        ctx.close()
+    for a, b in zip(*out):
+        assert a[0] == b[0]
+        assert abs(a[1] - b[1]) <= 1e-12 * abs(a[1]) and a[2] == b[2]   # sums of other walks, the same maximum
+        assert np.array_equal(a[3], b[3])
