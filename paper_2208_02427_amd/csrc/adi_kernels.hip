@@ -769,6 +769,168 @@ hipError_t launch_zebra_lines(const LineArgsT<T>& a, int dir, hipStream_t s) {
 template hipError_t launch_zebra_lines<double>(const LineArgsT<double>&, int, hipStream_t);
 template hipError_t launch_zebra_lines<float>(const LineArgsT<float>&, int, hipStream_t);
 
+// ------------------------------------------- small-level tail of a zebra cycle
+// All levels from one that fits LDS with its hierarchy down to the coarsest
+// and back, in one workgroup.  As launches a level takes eight line halves, a
+// restriction and a correction, 4 to 7 us each whatever its size (bound by
+// the launch and one dependent chain of loads, barriers and eliminations);
+// here they are the same device code on LDS, without the launch and the memory
+// round trips.  256 threads: the first level's lines of one parity are about
+// that many blocks, and four wavefronts make cheap barriers.  Every value is
+// produced by the expressions of the separate kernels, so the result is theirs
+// bit for bit.  LDS: the line solvers' scratch, then every level's iterate and
+// right-hand side, then the coarsest solve's.
+constexpr int kZebraScratch = kZebraTail * kSegBS + kSegHead;
+static_assert(kZebraScratch % 2 == 0 && kZebraScratch >= 5 * kZebraTail + kSegHead, "line scratch");
+
+template <typename T>
+__global__ __launch_bounds__(kZebraTail) void k_zebra_tail(ZebraTailArgs<T> S) {
+    if (S.ctrl != nullptr && S.ctrl->done) return;
+    extern __shared__ double tail_lds[];
+    constexpr int NT = kZebraTail;
+    T* const lds = reinterpret_cast<T*>(tail_lds);
+    const int tid = threadIdx.x;
+    {
+        const ZebraTailLevel<T>& L = S.lv[0];
+        const float inv = 1.0f / (float)L.P;
+        for (int q = tid; q < L.n * L.P; q += NT) {
+            const int j = seg_div(q, inv), i = q - j * L.P;
+            lds[L.ou + q] = T(0);
+            lds[L.of + q] = i < L.m ? S.b[(size_t)j * S.P + i] : T(0);
+        }
+    }
+    __syncthreads();
+    // x += P(e) on the interior of level l
+    const auto correct = [&](int l) {
+        const ZebraTailLevel<T>&F = S.lv[l], &C = S.lv[l + 1];
+        const float inv = 1.0f / (float)(F.m - 2);
+        for (int q = tid; q < (F.m - 2) * (F.n - 2); q += NT) {
+            const int jj = seg_div(q, inv);
+            const int j = jj + 1, i = q - jj * (F.m - 2) + 1;
+            const T* e = lds + C.ou + (j >> 1) * C.P + (i >> 1);
+            const T lo0 = e[0], lo1 = e[i & 1], hi0 = e[(j & 1) * C.P], hi1 = e[(j & 1) * C.P + (i & 1)];
+            T p;
+            if (j & 1)
+                p = (i & 1) ? ((lo0 + lo1) + (hi0 + hi1)) * T(0.25) : (lo0 + hi0) * T(0.5);
+            else
+                p = (i & 1) ? (lo0 + lo1) * T(0.5) : lo0;
+            T* x = lds + F.ou + j * F.P + i;
+            *x = *x + p;
+        }
+        __syncthreads();
+    };
+    int l = 0;
+    bool up = false;
+    for (;;) {
+        const ZebraTailLevel<T>& L = S.lv[l];
+        LineArgsT<T> A{};
+        A.u = lds + L.ou;
+        A.f = lds + L.of;
+        A.m = L.m;
+        A.n = L.n;
+        A.P = L.P;
+        A.cx = L.cx;
+        A.cy = L.cy;
+        A.d = L.d;
+        A.omega = S.omega;
+        const int halves = 4 * (up ? S.nu2 : S.nu1);
+#pragma unroll 1
+        for (int h = 0; h < halves; ++h) {
+            A.parity = 1 - (h & 1);
+            const int first = A.parity ? 1 : 2;
+            if ((h & 2) == 0) {
+                A.seg = L.seg[0];
+                const int W = seg_lines_of(0, L.m - 2, NT);
+                for (int t = 0; first + 2 * t * W <= L.n - 2; ++t) {
+                    adi_rows_seg<T, NT>(A, nullptr, t, lds);
+                    __syncthreads();
+                }
+            } else {
+                A.seg = L.seg[1];
+                const int W = seg_lines_of(1, L.n - 2, NT);
+                for (int t = 0; first + 2 * t * W <= L.m - 2; ++t) {
+                    adi_cols_seg<T, NT>(A, nullptr, t, lds);
+                    __syncthreads();
+                }
+            }
+        }
+        if (up) {
+            if (l == 0) break;
+            --l;
+            correct(l);
+            continue;
+        }
+        // residual and its full weighting: the coarse right-hand side, and a zero start
+        const ZebraTailLevel<T>& C = S.lv[l + 1];
+        const T cx = (T)L.cx, cy = (T)L.cy, d = (T)L.d;
+        const float inv = 1.0f / (float)C.P;
+        for (int q = tid; q < C.n * C.P; q += NT) {
+            const int J = seg_div(q, inv), I = q - J * C.P;
+            T v = 0;
+            if (I >= 1 && I <= C.m - 2 && J >= 1 && J <= C.n - 2) {
+                const T* x = lds + L.ou + 2 * J * L.P + 2 * I;
+                const T* f = lds + L.of + 2 * J * L.P + 2 * I;
+                const auto res = [&](int a, int b) -> T {
+                    const T* c = x + b * L.P + a;
+                    return f[b * L.P + a] - fma(-d, c[0], fma(cy, c[-L.P] + c[L.P], cx * (c[-1] + c[1])));
+                };
+                v = (fma(T(4), res(0, 0), T(2) * ((res(-1, 0) + res(1, 0)) + (res(0, -1) + res(0, 1)))) +
+                     ((res(-1, -1) + res(1, -1)) + (res(-1, 1) + res(1, 1)))) * T(0.0625);
+            }
+            lds[C.of + q] = v;
+            lds[C.ou + q] = T(0);
+        }
+        __syncthreads();
+        ++l;
+        if (l == S.nlev - 1) {
+            CoarseArgs<T> B{};
+            B.b = lds + C.of;
+            B.out = lds + C.ou;
+            B.minv = S.minv;
+            B.work = S.work;
+            B.bw = S.bw;
+            B.ifast = S.ifast;
+            B.m = C.m;
+            B.n = C.n;
+            B.P = C.P;
+            B.cx = C.cx;
+            B.cy = C.cy;
+            coarse_block<T>(B, tail_lds + S.rhs);
+            __syncthreads();
+            up = true;
+            --l;
+            correct(l);
+        }
+    }
+    const ZebraTailLevel<T>& L = S.lv[0];
+    const float inv = 1.0f / (float)L.m;
+    for (int q = tid; q < L.n * L.m; q += NT) {
+        const int j = seg_div(q, inv), i = q - j * L.m;
+        S.out[(size_t)j * S.P + i] = lds[L.ou + j * L.P + i];
+    }
+}
+
+template <typename T>
+hipError_t launch_zebra_tail(const ZebraTailArgs<T>& a, hipStream_t s) {
+    if (a.nlev < 2 || a.nlev > kMaxSub) return hipErrorInvalidValue;
+    for (int k = 0; k + 1 < a.nlev; ++k)
+        if (!seg_fits(0, a.lv[k].m - 2) || !seg_fits(1, a.lv[k].n - 2) ||
+            seg_lines_of(0, a.lv[k].m - 2, kZebraTail) < 1 || seg_lines_of(1, a.lv[k].n - 2, kZebraTail) < 1)
+            return hipErrorInvalidValue;
+    k_zebra_tail<T><<<1, kZebraTail, a.lds_bytes, s>>>(a);
+    return hipGetLastError();
+}
+template hipError_t launch_zebra_tail<double>(const ZebraTailArgs<double>&, hipStream_t);
+template hipError_t launch_zebra_tail<float>(const ZebraTailArgs<float>&, hipStream_t);
+
+hipError_t zebra_tail_set_lds_limit(int bytes) {
+    const hipError_t e =
+        hipFuncSetAttribute((const void*)k_zebra_tail<double>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    return e != hipSuccess ? e
+                           : hipFuncSetAttribute((const void*)k_zebra_tail<float>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
 template <typename T>
 static void launch_batch_seg(int kind, int code, const BatchItem* items, const int* tmap, int total, int blocks,
                              hipStream_t s) {

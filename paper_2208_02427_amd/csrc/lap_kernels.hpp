@@ -466,6 +466,35 @@ hipError_t launch_adi_cols(const LineArgs& a, hipStream_t s);
 template <typename T>
 hipError_t launch_zebra_lines(const LineArgsT<T>& a, int dir, hipStream_t s);
 
+// The small-level tail of a zebra V-cycle in one workgroup of kZebraTail
+// threads, every level in LDS (adi_kernels.hip): from a zero start on the
+// first of nlev levels down to the coarsest and back.
+constexpr int kZebraTail = 256;
+template <typename T>
+struct ZebraTailLevel {
+    int m, n, P;             // P: LDS pitch (even)
+    int ou, of;              // iterate and right-hand side (elements of T, even)
+    double cx, cy, d;
+    const T* seg[2];         // segment tables of its rows and columns
+};
+template <typename T>
+struct ZebraTailArgs {
+    T* out;                  // the first level's result and right-hand side
+    const T* b;
+    const Ctrl* ctrl;
+    const double* minv;      // coarsest solve, as in CoarseArgs
+    double* work;
+    int bw, ifast;
+    int P, nlev, nu1, nu2;
+    int rhs;                 // LDS offset in doubles of the coarsest solve's right-hand side
+    int lds_bytes;
+    double omega;
+    ZebraTailLevel<T> lv[kMaxSub];
+};
+template <typename T>
+hipError_t launch_zebra_tail(const ZebraTailArgs<T>& a, hipStream_t s);
+hipError_t zebra_tail_set_lds_limit(int bytes);
+
 // Segmented line solver.  A line of K unknowns is cut into S blocks of
 // kSegL unknowns, each followed by one separator unknown (the last block
 // holds the remaining 0..kSegL).  Every block is solved on its own with zero

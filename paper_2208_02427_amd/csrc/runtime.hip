@@ -471,6 +471,7 @@ struct lap_grid {
     float* ztab32 = nullptr;
     std::vector<char> upload;        // host copy of what grid creation uploads (alive while that copy is in flight)
     bool zebra_ok = false;
+    bool ztail = false;              // the running solve takes its zebra cycles' small levels in one launch
     bool pdef = false;               // the running mixed solve uses the post-smoothing + defect pass
     lap_opts batch_opts{};
     MergedRun mr;                    // the running solve, if it takes one finest pass per cycle
@@ -559,6 +560,7 @@ struct HierView {
     bool zero_start0 = false;  // level 0 starts from zero (error equation) or holds the iterate
     int root = 0;              // level of the cycle's root (full multigrid roots cycles on coarse levels)
     int sub_root = -1;         // level whose whole sub-V-cycle runs as one LDS-resident launch
+    int ztail = -1;                  // zebra cycles: first level of the one-launch tail, or -1
 };
 
 // Patches of a smoothed level and LDS bytes of a subtree rooted at level l:
@@ -669,6 +671,48 @@ hipError_t enq_subtree(lap_grid* g, int l, T* out, const T* b, double omega, int
     const SubtreeArgs<T> a = subtree_args<T>(g, l, out, b, omega, nus);
     const double bytes = 2.0 * sizeof(T) * g->geo[l].m * (double)g->geo[l].n;
     return g->ctx->timed(KC_SUBTREE, false, bytes, [&]() { return launch_subtree<T>(a, g->ctx->stream); });
+}
+
+// LDS of a zebra cycle's tail from level l on; fills the levels' places if a is given.
+template <typename T>
+size_t zebra_tail_lds(const lap_grid* g, int l, ZebraTailArgs<T>* a) {
+    const int L = (int)g->geo.size();
+    size_t e = (size_t)kZebraTail * (kSegL + 2) + 4 * kSegL;   // the line solvers' scratch (kZebraScratch)
+    for (int k = l; k < L; ++k) {
+        const LevelGeo& G = g->geo[k];
+        const int P = (G.m + 1) & ~1;
+        const size_t sz = (size_t)G.n * P;
+        if (a != nullptr) {
+            ZebraTailLevel<T>& v = a->lv[k - l];
+            v.m = G.m;
+            v.n = G.n;
+            v.P = P;
+            v.ou = (int)e;
+            v.of = (int)(e + sz);
+        }
+        e += 2 * sz;
+    }
+    const size_t at = (e * sizeof(T) + 7) / 8;
+    if (a != nullptr) a->rhs = (int)at;
+    return at * 8 + (g->coarse_bw == 0 ? g->geo.back().interior() * sizeof(double) : 0);
+}
+
+// First level of a zebra cycle's one-launch tail, or -1: as for the subtree
+// of red-black cycles, below level 0, under the same switch and node limit.
+// 641 x 385 (FP64, tail from 81 x 49): 3.50 -> 3.12 ms a solve of 8 cycles, the tail
+// 122 us where its 32 launches took 4 to 10 us each.
+template <typename T>
+int zebra_root(const lap_grid* g) {
+    const lap_ctx* c = g->ctx;
+    const int L = (int)g->geo.size();
+    if (c->sub_max_nodes == 0) return -1;
+    for (int l = std::max(1, L - kMaxSub); l < L - 1; ++l) {
+        const LevelGeo& G = g->geo[l];
+        if (c->sub_max_nodes > 0 && (int64_t)G.m * G.n > c->sub_max_nodes) continue;
+        if (seg_count(G.m - 2) > kZebraTail || seg_count(G.n - 2) > kZebraTail) continue;
+        if (zebra_tail_lds<T>(g, l, nullptr) <= (size_t)c->lds_max) return l;
+    }
+    return -1;
 }
 
 template <typename T> constexpr int dt_of() { return sizeof(T) == 8 ? 0 : 1; }
@@ -834,7 +878,7 @@ hipError_t enq_residual_norm(lap_grid* g, int l, const T* u, const T* f) {
 // pre-smoothing and restriction of level l, then every grid's coarsest
 // solve, then the post-smoothing of level l from coarse to fine.
 enum OpKind { OP_SWEEP, OP_RESTRICT, OP_COARSE, OP_FINALIZE, OP_RESNORM, OP_DEFECT, OP_ADI_ROWS, OP_ADI_COLS,
-              OP_SUBTREE, OP_POSTDEF, OP_BOUNDARY };
+              OP_SUBTREE, OP_POSTDEF, OP_BOUNDARY, OP_ZTAIL };
 
 struct Op {
     long key;
@@ -1017,8 +1061,13 @@ int plan_vcycle_zebra(lap_grid* g, HierView<T>& H, int l, const lap_opts& o, boo
         push_op<T>(ops, KEY_COARSE, OP_COARSE, l, 0, zero_start ? nullptr : U, U, b, nullptr, nullptr, 0.0);
         return 0;
     }
+    if (l == H.ztail) {
+        push_op<T>(ops, KEY_COARSE, OP_ZTAIL, l, o.nu1 | (o.nu2 << 8), nullptr, U, b, nullptr, nullptr, o.omega);
+        return 0;
+    }
     push_zebra<T>(g, l, U, b, o.omega, o.nu1, key_pre(l, 0), ops);
-    push_op<T>(ops, key_restrict(l), OP_RESTRICT, l, 0, U, H.u0[l + 1], b, nullptr, H.b[l + 1], 0.0);
+    push_op<T>(ops, key_restrict(l), OP_RESTRICT, l, 0, U, l + 1 == H.ztail ? nullptr : H.u0[l + 1], b, nullptr,
+               H.b[l + 1], 0.0);
     plan_vcycle_zebra<T>(g, H, l + 1, o, false, PART_ALL, ops);
     push_op<T>(ops, key_post(l, 0), OP_SWEEP, l, SW_PROLONG | SW_PONLY, U, U, nullptr, H.u0[l + 1], nullptr, 0.0);
     push_zebra<T>(g, l, U, b, o.omega, o.nu2, key_post(l, 1), ops);
@@ -1134,6 +1183,7 @@ HierView<double> view64(lap_grid* g, int nu1) {
     }
     H.zero_start0 = false;
     H.sub_root = subtree_root<double>(g, 1, nu1);
+    H.ztail = g->ztail ? zebra_root<double>(g) : -1;
     return H;
 }
 
@@ -1150,6 +1200,7 @@ HierView<float> view32(lap_grid* g, int nu1) {
     }
     H.zero_start0 = true;
     H.sub_root = subtree_root<float>(g, 0, nu1);
+    H.ztail = g->ztail ? zebra_root<float>(g) : -1;
     return H;
 }
 
@@ -1570,6 +1621,37 @@ hipError_t enq_zebra(lap_grid* g, const Op& op, int dir) {
                          [&]() { return launch_zebra_lines<T>(a, dir, g->ctx->stream); });
 }
 
+template <typename T>
+hipError_t enq_zebra_tail(lap_grid* g, int l, T* out, const T* b, double omega, int nus) {
+    ZebraTailArgs<T> a{};
+    a.lds_bytes = (int)zebra_tail_lds<T>(g, l, &a);
+    a.nlev = (int)g->geo.size() - l;
+    for (int k = 0; k < a.nlev; ++k) {
+        const LineArgsT<T> r = zebra_args<T>(g, l + k, nullptr, nullptr, omega, 0, 0);
+        ZebraTailLevel<T>& v = a.lv[k];
+        v.cx = r.cx;
+        v.cy = r.cy;
+        v.d = r.d;
+        if (k + 1 < a.nlev) {
+            v.seg[0] = r.seg;
+            v.seg[1] = r.seg + kSegTab;
+        }
+    }
+    a.out = out;
+    a.b = b;
+    a.ctrl = kctrl(g);
+    a.minv = g->minv;
+    a.work = g->coarse_work;
+    a.bw = g->coarse_bw;
+    a.ifast = g->coarse_ifast;
+    a.P = g->geo[l].P;
+    a.nu1 = nus & 255;
+    a.nu2 = nus >> 8;
+    a.omega = omega;
+    const double bytes = 2.0 * sizeof(T) * g->geo[l].m * (double)g->geo[l].n;
+    return g->ctx->timed(KC_SUBTREE, false, bytes, [&]() { return launch_zebra_tail<T>(a, g->ctx->stream); });
+}
+
 // Launch one recorded operation of grid g.
 hipError_t exec_op_body(lap_grid* g, const Op& op) {
     const int l = op.level;
@@ -1617,6 +1699,10 @@ hipError_t exec_op_body(lap_grid* g, const Op& op) {
             if (op.dt == 0)
                 return enq_subtree<double>(g, l, (double*)op.out, (const double*)op.f, op.omega, op.flags);
             return enq_subtree<float>(g, l, (float*)op.out, (const float*)op.f, op.omega, op.flags);
+        case OP_ZTAIL:
+            if (op.dt == 0)
+                return enq_zebra_tail<double>(g, l, (double*)op.out, (const double*)op.f, op.omega, op.flags);
+            return enq_zebra_tail<float>(g, l, (float*)op.out, (const float*)op.f, op.omega, op.flags);
         case OP_BOUNDARY: {
             const LevelGeo& G = g->geo[l];
             return launch_level_boundary((double*)op.out, (double*)op.bc, op.flags ? g->psi[0] : nullptr, G.m, G.n,
@@ -1964,6 +2050,8 @@ lap_status prepare(lap_grid* g, const lap_opts& o, bool init = true) {
         if (st != LAP_OK) return st;
     }
     g->step_idx = 0;
+    // a batch merges its grids' launches level by level instead
+    g->ztail = init && o.method == LAP_MG && o.smoother == LAP_SMOOTH_ZEBRA;
     g->mr = MergedRun{};
     g->mr.on = init && merged_ok(g, o);   // a batch runs its own plans
     g->pdef = postdef_ok(g, o);   // fixed for the whole solve
@@ -2379,7 +2467,8 @@ lap_status lap_ctx_create(void* dev_arena, size_t arena_bytes, void* hip_stream,
         if (hipDeviceGetAttribute(&optin, hipDeviceAttributeSharedMemPerBlockOptin, dev) != hipSuccess) optin = 0;
         lds = std::max(lds, optin);
         if (lds > 0) {
-            if (subtree_set_lds_limit(lds) == hipSuccess && paper_set_lds_limit(lds) == hipSuccess) {
+            if (subtree_set_lds_limit(lds) == hipSuccess && paper_set_lds_limit(lds) == hipSuccess &&
+                zebra_tail_set_lds_limit(lds) == hipSuccess) {
                 c->lds_max = lds;
             } else {
                 (void)hipGetLastError();

@@ -180,3 +180,29 @@ def test_zebra_argument_errors():
     with pytest.raises(LapError):
         g.solve("mg", smoother=7, raise_on_fail=True)
     g.destroy()
+
+
+@pytest.mark.parametrize("m,n,beta,src", [(641, 385, 2.0, True), (81, 49, 2.0, True), (161, 81, 0.4, False),
+                                          (33, 17, 5.0, True), (385, 17, 1.0, False), (17, 257, 0.2, True)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_zebra_tail_in_one_launch_bitwise(m, n, beta, src, precision):
+    """The small levels in one launch against a launch per line half, with
+    the tail starting at several levels: lines of one to 24 blocks, one and
+    several tiles a half, dense and separable coarsest solves."""
+    torch, lap = need_gpu()
+    psi, f, dx, dy = _problem(m, n, beta, src, m * 7 + n)
+    ctx = _ctx(torch, lap)
+    out = []
+    for nodes in (0, 300, 1200, -1):
+        say("zebra tail", m, n, precision, nodes)
+        ctx.set_subtree(nodes)
+        g = ctx.grid(to_dev(torch, psi), to_dev(torch, f) if src else None, dx, dy)
+        for _ in range(3):   # the third solve replays a captured graph
+            g.write(to_dev(torch, psi))
+            info = g.solve("mg", precision=precision, smoother="zebra", nu1=1, nu2=2, tol=0.0, max_iter=3)
+        out.append((info["rel_res_l2"], g.read().cpu().numpy()))
+        g.destroy()
+    ctx.set_subtree(-1)
+    for rel, u in out[1:]:
+        assert rel == out[0][0]
+        assert np.array_equal(u, out[0][1])
