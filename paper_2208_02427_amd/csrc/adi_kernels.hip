@@ -27,8 +27,18 @@
 // sequential solver follows the plain recurrence (divisions, no fused
 // multiply-add); the segmented one multiplies by tabulated reciprocals and
 // fuses, so the two agree to rounding.
+//
+// The segmented solver is bound by latency: a wavefront's round trips, and the
+// few thousand instructions of its serial elimination.  Hence no branch on
+// lengths inside a block (addresses are clamped and values selected): with one a
+// row, the column kernel waited for each of its 16 rows before it asked
+// for the next, and every table value was an LDS round trip in the chain.
+// Whole solves, branches a row against none: zebra multigrid of 641 x 385 3.12 ->
+// 2.52 ms (columns 9.8 -> 6.4 us a launch, rows 7.2 -> 6.1), 20 ADI iterations of
+// 2049 x 1500 1.38 -> 1.24 ms.
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "lap_kernels.hpp"
 #include "stencil_tiles.hpp"
@@ -272,26 +282,50 @@ __device__ __forceinline__ T seg_rhs(const LineArgsT<T>& A, T cc, T own, T nb, T
 }
 
 // Forward elimination of one block given its right-hand sides r[0..len)
-// (len <= kSegL); leaves the block's zero-end solution in r, returns its
-// last value in *last.  Tb: the table's block part, in LDS.
+// (len <= kSegL, zeros behind); leaves the block's zero-end solution in r,
+// returns its last value in *last.  Tb: the table's block part, in LDS.
+// Without branches on len: a branch a row kept the table's reads from being
+// issued ahead, an LDS round trip for each.  What the rows behind len hold
+// reaches nothing: their coefficient and value enter the substitution as zeros.
 template <typename T>
 __device__ __forceinline__ void seg_block(const T* Tb, T E, int len, T (&r)[kSegL], T* last) {
+    T ip[kSegL], cq[kSegL];
+#pragma unroll
+    for (int k = 0; k < kSegL; ++k) {
+        ip[k] = Tb[SEG_IPIV + k];
+        cq[k] = Tb[SEG_CQ + k];
+    }
     T z = 0;
 #pragma unroll
-    for (int k = 0; k < kSegL; ++k)
-        if (k < len) {
-            z = fma(E, z, r[k]) * Tb[SEG_IPIV + k];
-            r[k] = z;
-        }
+    for (int k = 0; k < kSegL; ++k) {
+        z = fma(E, z, r[k]) * ip[k];
+        r[k] = z;
+    }
     T x = 0, e = 0;
 #pragma unroll
-    for (int k = kSegL - 1; k >= 0; --k)
-        if (k < len) {
-            x = fma(Tb[SEG_CQ + k], x, r[k]);
-            r[k] = x;
-            if (k == len - 1) e = x;
-        }
+    for (int k = kSegL - 1; k >= 0; --k) {
+        x = fma(k < len - 1 ? cq[k] : T(0), x, k < len ? r[k] : T(0));
+        r[k] = x;
+        e = k == len - 1 ? x : e;
+    }
     *last = e;
+}
+
+// The block's solution from its zero-end solution y and the values xl, xr
+// of the separators beside it (full: a separator follows it).
+template <typename T>
+__device__ __forceinline__ void seg_apply(const T* Tb, bool full, T xl, T xr, T (&y)[kSegL]) {
+    T g[kSegL], h[kSegL];
+#pragma unroll
+    for (int k = 0; k < kSegL; ++k) {
+        g[k] = Tb[(full ? SEG_G : SEG_GL) + k];
+        h[k] = Tb[SEG_G + kSegL - 1 - k];
+    }
+#pragma unroll
+    for (int k = 0; k < kSegL; ++k) {
+        const T t = fma(xl, g[k], y[k]);
+        y[k] = full ? fma(xr, h[k], t) : t;
+    }
 }
 
 // Reduced system of one line, its unknown p held by one thread (act; NR
@@ -492,18 +526,13 @@ static __device__ void adi_rows_seg(const LineArgsT<T>& A, const Ctrl* ctrl, int
         __syncthreads();
     }
     if (act) {
+        // (slots behind len are the block's own and read by no one)
         const T xl = s > 0 ? blk[kSegL + 1 - kSegBS] : T(0);
-        if (s < S - 1) {
-            const T xr = blk[kSegL + 1];
+        const T xr = sep ? blk[kSegL + 1] : T(0);
+        seg_apply<T>(Tb, sep, xl, xr, y);
 #pragma unroll
-            for (int k = 0; k < kSegL; ++k)
-                blk[k] = fma(xr, Tb[SEG_G + kSegL - 1 - k], fma(xl, Tb[SEG_G + k], y[k]));
-            blk[kSegL] = xr;
-        } else {
-#pragma unroll
-            for (int k = 0; k < kSegL; ++k)
-                if (k < len) blk[k] = fma(xl, Tb[SEG_GL + k], y[k]);
-        }
+        for (int k = 0; k < kSegL; ++k) blk[k] = y[k];
+        if (sep) blk[kSegL] = xr;
     }
     __syncthreads();
     const T w = (T)A.omega;
@@ -576,30 +605,50 @@ static __device__ void adi_cols_seg(const LineArgsT<T>& A, const Ctrl* ctrl, int
         T head = 0, tail = 0;
         if (s == 0) head = A.u[i];
         if (s == S - 1 || k0 + kSegL == K - 1) tail = A.u[(size_t)(A.n - 1) * P + i];
-        const auto node = [&](int k, T& own, T& r) {
-            const T2 q = *reinterpret_cast<const T2*>(up + (size_t)k * P);
-            const T t = up[(ptrdiff_t)((size_t)k * P) + third];
-            own = odd ? q.y : q.x;
-            // the same sum of the west and east neighbours
-            const T nb = odd ? q.x + t : t + q.y;
-            r = seg_rhs<T>(A, cc, own, nb, fp != nullptr ? fp[(size_t)k * P] : T(0));
+        // rows behind the line's last one are read clamped to it, so that the
+        // loads have no branches between them and kG rows' are in flight
+        constexpr int kG = NT >= 1024 ? 4 : 8;
+        const int klast = K - 1 - k0;                      // >= 0 wherever a row is used
+        const auto rows = [&](auto has_f, int g0) {
+            constexpr bool HF = decltype(has_f)::value;
+            T2 q[kG];
+            T t[kG], fv[kG];
+#pragma unroll
+            for (int v = 0; v < kG; ++v) {
+                const ptrdiff_t o = (ptrdiff_t)min(g0 + v, klast) * (ptrdiff_t)P;
+                q[v] = *reinterpret_cast<const T2*>(up + o);
+                t[v] = up[o + third];
+                fv[v] = HF ? fp[o] : T(0);
+            }
+#pragma unroll
+            for (int v = 0; v < kG; ++v) {
+                const int k = g0 + v;
+                const T own = odd ? q[v].y : q[v].x;
+                // the same sum of the west and east neighbours
+                const T nb = odd ? q[v].x + t[v] : t[v] + q[v].y;
+                const T r = seg_rhs<T>(A, cc, own, nb, fv[v]);
+                if (k < kSegL) {
+                    old[k] = own;
+                    y[k] = k < len ? r : T(0);
+                } else {
+                    osep = own;
+                    rsep = r;
+                }
+            }
         };
 #pragma unroll
-        for (int k = 0; k < kSegL; ++k) {
-            old[k] = 0;
-            y[k] = 0;
-            if (k < len) node(k, old[k], y[k]);
+        for (int g0 = 0; g0 < kSegL + 1; g0 += kG) {
+            if (fp != nullptr)
+                rows(std::true_type{}, g0);
+            else
+                rows(std::false_type{}, g0);
         }
         if (s == 0) y[0] = y[0] + E * head;
         if (len > 0 && k0 + len == K) {
 #pragma unroll
-            for (int k = 0; k < kSegL; ++k)
-                if (k == len - 1) y[k] = y[k] + E * tail;
+            for (int k = 0; k < kSegL; ++k) y[k] = k == len - 1 ? y[k] + E * tail : y[k];
         }
-        if (s < S - 1) {
-            node(kSegL, osep, rsep);
-            if (k0 + kSegL == K - 1) rsep = rsep + E * tail;
-        }
+        if (s < S - 1 && k0 + kSegL == K - 1) rsep = rsep + E * tail;
     }
     if (seg_done(ctrl)) return;                        // uniform over the workgroup
     __syncthreads();                                   // the table is staged
@@ -621,22 +670,14 @@ static __device__ void adi_cols_seg(const LineArgsT<T>& A, const Ctrl* ctrl, int
         const T w = (T)A.omega;
         const T xl = s > 0 ? yF[me - W] : T(0);
         T* up = A.u + (size_t)(k0 + 1) * P + i;
-        if (s < S - 1) {
-            const T xr = yF[me];
+        const T xr = sep ? yF[me] : T(0);
+        seg_apply<T>(Tb, sep, xl, xr, y);
 #pragma unroll
-            for (int k = 0; k < kSegL; ++k) {
-                const T t = fma(xr, Tb[SEG_G + kSegL - 1 - k], fma(xl, Tb[SEG_G + k], y[k]));
-                up[(size_t)k * P] = (A.form == 0) ? old[k] + w * (t - old[k]) : t;
-            }
-            up[(size_t)kSegL * P] = (A.form == 0) ? osep + w * (xr - osep) : xr;
-        } else {
-#pragma unroll
-            for (int k = 0; k < kSegL; ++k)
-                if (k < len) {
-                    const T t = fma(xl, Tb[SEG_GL + k], y[k]);
-                    up[(size_t)k * P] = (A.form == 0) ? old[k] + w * (t - old[k]) : t;
-                }
+        for (int k = 0; k < kSegL; ++k) {
+            const T t = (A.form == 0) ? old[k] + w * (y[k] - old[k]) : y[k];
+            if (k < len) up[(size_t)k * P] = t;
         }
+        if (sep) up[(size_t)kSegL * P] = (A.form == 0) ? osep + w * (xr - osep) : xr;
     }
 }
 
