@@ -392,12 +392,16 @@ __device__ __forceinline__ T seg_scan(T ER, T ip, T cq, int reach, int NR, int p
     return b;
 }
 
-// The table's block part (SEG_IPIV .. SEG_GL), copied to LDS while the
-// field's loads are in flight: the elimination then waits for no scalar load.
+// The table's block part (SEG_IPIV .. SEG_GL) goes to LDS: read first, before
+// the field's loads, and stored behind them, so that neither waits for it.
 constexpr int kSegHead = 4 * kSegL;
 template <typename T>
-__device__ __forceinline__ void seg_stage_table(const T* Tb, T* tab) {
-    if (threadIdx.x < kSegHead) tab[threadIdx.x] = Tb[threadIdx.x];
+__device__ __forceinline__ T seg_table_load(const T* Tb) {
+    return Tb[min((int)threadIdx.x, kSegHead - 1)];
+}
+template <typename T>
+__device__ __forceinline__ void seg_table_store(T v, T* tab) {
+    if (threadIdx.x < kSegHead) tab[threadIdx.x] = v;
 }
 
 // Two consecutive values of a row (aligned to one value only).
@@ -456,7 +460,7 @@ static __device__ void adi_rows_seg(const LineArgsT<T>& A, const Ctrl* ctrl, int
         ip = Tg[SEG_IPIVR + s];
         cq = Tg[SEG_CQR + s];
     }
-    seg_stage_table<T>(Tg, Tb);
+    const T tv = seg_table_load<T>(Tg);
 #pragma unroll
     for (int g = 0; g < kU; g += kG) {
         T2 up[kG], dn[kG], fv[kG];
@@ -486,7 +490,10 @@ static __device__ void adi_rows_seg(const LineArgsT<T>& A, const Ctrl* ctrl, int
                 // K = 1 or 2: a pair holding both ends (its left end is added below)
             }
         }
-        if (g == 0 && seg_done(ctrl)) return;      // uniform over the workgroup
+        if (g == 0) {
+            if (seg_done(ctrl)) return;            // uniform over the workgroup
+            seg_table_store<T>(tv, Tb);
+        }
 #pragma unroll
         for (int v = 0; v < kG; ++v) {
             if (slot[v] < 0) continue;
@@ -593,7 +600,7 @@ static __device__ void adi_cols_seg(const LineArgsT<T>& A, const Ctrl* ctrl, int
     const int me = s * W + c;
     T y[kSegL], old[kSegL];
     T osep = 0, rsep = 0, e = 0, ip = 0, cq = 0;
-    seg_stage_table<T>(Tg, Tb);
+    const T tv = seg_table_load<T>(Tg);
     if (sep) {
         ip = Tg[SEG_IPIVR + s];
         cq = Tg[SEG_CQR + s];
@@ -651,7 +658,8 @@ static __device__ void adi_cols_seg(const LineArgsT<T>& A, const Ctrl* ctrl, int
         if (s < S - 1 && k0 + kSegL == K - 1) rsep = rsep + E * tail;
     }
     if (seg_done(ctrl)) return;                        // uniform over the workgroup
-    __syncthreads();                                   // the table is staged
+    seg_table_store<T>(tv, Tb);
+    __syncthreads();
     if (act) {
         seg_block<T>(Tb, E, len, y, &e);
         yF[me] = len > 0 ? y[0] : T(0);
@@ -744,7 +752,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_adi_cols(const BatchItem* item
 // Segmented solver over all grids: tiles of seg_lines lines of one grid,
 // dealt XCD-contiguously (neighbouring tiles share boundary lines).
 template <typename T, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_batch_adi_rows_seg(const BatchItem* items, const int* tmap, int total) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_batch_adi_rows_seg(const BatchItem* items, const int* tmap, int total) {
     __shared__ T lds[NT * kSegBS + kSegHead];
     for (int t = xcd_remap(blockIdx.x, gridDim.x); t < total; t += gridDim.x) {
         const BatchItem& it = items[tmap[t]];
