@@ -537,7 +537,7 @@ __device__ __forceinline__ void restrict_tile(const RestrictArgs<T>& A, int tile
 // canonical 18-row chunks, HIP events: f = 0 106 us with two rows ahead, 95 us
 // with a ring of 6 (66 registers, 7 waves per SIMD), 99-104 with 8 or 9; with
 // a source 185 -> 178 us.
-constexpr int kResRing = 6;
+constexpr int kResRing = 12;
 
 template <typename T, int V>
 __device__ __forceinline__ void residual_tile(const ResidualArgs<T>& A, int tile, int lane) {
