@@ -2042,18 +2042,22 @@ int ctrl_step(const lap_opts& o) { return (o.method == LAP_MG) ? 1 : o.check_eve
 // finds: the iterate has seen max_iter iterations.
 bool test_is_last(const lap_opts& o, int s) { return (int64_t)s * ctrl_step(o) >= o.max_iter; }
 
-// Per-solve set-up of one grid; init = false leaves the control block to the
-// caller (a batch resets all of them in one launch).
-lap_status prepare(lap_grid* g, const lap_opts& o, bool init = true) {
-    if (init) {
+// Who drives a solve: solve_one, with a schedule of its own (one finest pass
+// per cycle, the zebra tail); a tick, whose steps are merged with other
+// grids' (plan_step's schedule); or a batch, which is a tick that resets all
+// its grids' control blocks in one launch of its own.
+enum class Driver { ALONE, TICK, BATCH };
+
+// Per-solve set-up of one grid.
+lap_status prepare(lap_grid* g, const lap_opts& o, Driver by) {
+    if (by != Driver::BATCH) {
         lap_status st = init_ctrl(g, o, ctrl_step(o));
         if (st != LAP_OK) return st;
     }
     g->step_idx = 0;
-    // a batch merges its grids' launches level by level instead
-    g->ztail = init && o.method == LAP_MG && o.smoother == LAP_SMOOTH_ZEBRA;
+    g->ztail = by == Driver::ALONE && o.method == LAP_MG && o.smoother == LAP_SMOOTH_ZEBRA;
     g->mr = MergedRun{};
-    g->mr.on = init && merged_ok(g, o);   // a batch runs its own plans
+    g->mr.on = by == Driver::ALONE && merged_ok(g, o);
     g->pdef = postdef_ok(g, o);   // fixed for the whole solve
     g->e_idx = vcycle_result_index(g->ctx, o);
     if (o.method == LAP_MG && o.precision == LAP_MIXED && o.inner > 1 && !g->l32.empty()) {
@@ -2256,7 +2260,9 @@ lap_status fixup(lap_grid* g, const lap_opts& o, const Ctrl& h) {
     const size_t bytes = (size_t)g->n * g->P * 8;
     int rb = result_buffer(g, o, h);
     if (g->mr.on) {
-        const uint8_t at = h.checks > 0 ? g->mr.log[h.checks - 1] : 0;
+        if (h.checks < 1 || (size_t)h.checks > g->mr.log.size())
+            return fail(LAP_EINVAL, "internal error: a tested iterate without a record of its buffer");
+        const uint8_t at = g->mr.log[h.checks - 1];
         rb = at & 1;
         if (at & 2) {
             // the pass that tested the iterate went on to the next cycle: form it again
@@ -2376,7 +2382,7 @@ lap_status solve_one(lap_grid* g, const lap_opts& o, lap_info* info) {
     if (is_paper_method(o.method)) return solve_paper(g, o, info);
     if (mg_solve_ok(g, o)) return solve_small(g, o, info);
     const double t0 = now_s();
-    lap_status st = prepare(g, o);
+    lap_status st = prepare(g, o, Driver::ALONE);
     if (st != LAP_OK) return st;
     lap_ctx* c = g->ctx;
     c->rec_solve = c->timing ? c->solve_serial++ : -1;
@@ -3607,7 +3613,7 @@ extern "C" lap_status lap_solve_batch(lap_ctx* c, lap_grid* const* grids, int32_
     lap_opts po = *o;
     po.use_graph = 0;   // per-grid graphs are not used; the merged plans have their own
     for (int k = 0; k < count; ++k) {
-        lap_status st = prepare(grids[k], po, false);
+        lap_status st = prepare(grids[k], po, Driver::BATCH);
         if (st != LAP_OK) return st;
     }
     if (count > 0) {   // all control blocks reset in one launch
@@ -3735,7 +3741,7 @@ extern "C" lap_status lap_batch_step(lap_ctx* c, lap_grid* const* grids, int32_t
             go.use_graph = 0;
             lap_status st = validate_opts(g, go);
             if (st != LAP_OK) return st;
-            st = prepare(g, go);
+            st = prepare(g, go, Driver::TICK);
             if (st != LAP_OK) return st;
             g->batch_opts = go;
             g->batch_started = true;

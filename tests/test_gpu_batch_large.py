@@ -1,0 +1,78 @@
+"""FP64 grids on both sides of 2^21 interior nodes, from where on a grid solved
+alone takes one pass per cycle over its finest level: in a batch or in ticks
+it runs the merged plans, and ends where it ends alone, bit for bit."""
+import numpy as np
+import pytest
+
+from gpu_helpers import need_gpu, rand_problem, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1537, 1537), (129, 97), (2049, 1025), (1025, 1537)]   # 2.36e6, small, 2.10e6 (just above), 1.57e6
+
+
+def _problems(torch):
+    out = []
+    for k, (m, n) in enumerate(SHAPES):
+        psi, f, dx, dy = rand_problem(m, n, seed=90 + k, dx=1.0 / (m - 1), dy=1.1 / (m - 1), source=k % 2 == 0)
+        out.append((to_dev(torch, psi), to_dev(torch, f) if f is not None else None, dx, dy))
+    return out
+
+
+def _alone(torch, lap, probs, **kw):
+    ctx = lap.Context(arena_bytes=2 << 30)
+    out = []
+    for p, (m, n) in zip(probs, SHAPES):
+        say("large alone", m, n)
+        g = ctx.grid(*p, alloc=lap.LAP_ALLOC_FP64)
+        info = g.solve("mg", **kw)
+        out.append((info, g.read().cpu().numpy()))
+        g.destroy()
+    ctx.close()
+    return out
+
+
+def _same(info, u, ref):
+    for key in ("iterations", "status", "rel_res_l2", "res_l2", "res_linf", "res0_l2"):
+        assert info[key] == ref[0][key], key
+    assert np.array_equal(u, ref[1])
+
+
+@pytest.mark.parametrize("steps", [1, 3])
+def test_fp64_ticks_match_alone(steps):
+    torch, lap = need_gpu()
+    probs = _problems(torch)
+    alone = _alone(torch, lap, probs, tol=1e-9, max_iter=1000)
+    ctx = lap.Context(arena_bytes=2 << 30)
+    gs = [ctx.grid(*p, alloc=lap.LAP_ALLOC_FP64) for p in probs]
+    for g in gs:
+        g.set_tol(1e-9)
+    say("large ticks", SHAPES, steps)
+    left, infos = set(range(len(gs))), {}
+    for _ in range(60):
+        todo = sorted(left)
+        done, ins = ctx.batch_step([gs[k] for k in todo], precision="fp64", steps=steps)
+        for k, d, i in zip(todo, done, ins):
+            if d:
+                infos[k] = i
+                left.discard(k)
+        if not left:
+            break
+    assert not left
+    for k, g in enumerate(gs):
+        _same(infos[k], g.read().cpu().numpy(), alone[k])
+    ctx.close()
+
+
+@pytest.mark.parametrize("kw", [dict(tol=1e-9, max_iter=30), dict(tol=0.0, max_iter=3)])
+def test_fp64_batch_matches_alone(kw):
+    torch, lap = need_gpu()
+    probs = _problems(torch)
+    alone = _alone(torch, lap, probs, **kw)
+    ctx = lap.Context(arena_bytes=2 << 30)
+    gs = [ctx.grid(*p, alloc=lap.LAP_ALLOC_FP64) for p in probs]
+    say("large batch", SHAPES, kw)
+    infos = ctx.solve_batch(gs, method="mg", **kw)
+    for g, info, ref in zip(gs, infos, alone):
+        _same(info, g.read().cpu().numpy(), ref)
+    ctx.close()
