@@ -421,6 +421,7 @@ struct MergedRun {
     int cur = 0;                     // buffer of psi that the next step reads:
     bool pre = false;                // pre-smoothed, to be corrected by ec and post-smoothed, or an iterate
     const double* ec = nullptr;
+    bool forming = false;            // the tested iterate is being formed again, after the end of the solve
     // per step, where the iterate its test saw is: its buffer, or that buffer + 2 if it has to be
     // formed there from the other buffer and ec
     std::vector<uint8_t> log;
@@ -489,7 +490,11 @@ namespace {
 
 // The control block whose done flag the kernels of the operation being
 // launched test: a gate of a mixed step while one is set, else the solve's.
-inline Ctrl* kctrl(const lap_grid* g) { return g->op_ctrl != nullptr ? g->op_ctrl : g->ctrl; }
+// None while a finished solve forms its result again: the solve's stays done.
+inline Ctrl* kctrl(const lap_grid* g) {
+    if (g->mr.forming) return nullptr;
+    return g->op_ctrl != nullptr ? g->op_ctrl : g->ctrl;
+}
 
 struct Footprint {
     size_t bytes = 0;
@@ -2266,9 +2271,12 @@ lap_status fixup(lap_grid* g, const lap_opts& o, const Ctrl& h) {
         rb = at & 1;
         if (at & 2) {
             // the pass that tested the iterate went on to the next cycle: form it again
-            HIPCHK(launch_ctrl_init(g->ctrl, o.tol, o.stop, o.max_iter, 1, c->stream));
-            HIPCHK(exec_op(g, merged_post(g, o, 1 - rb)));
+            g->mr.forming = true;
+            const hipError_t e = exec_op(g, merged_post(g, o, 1 - rb));
+            g->mr.forming = false;
+            HIPCHK(e);
         }
+        g->mr = MergedRun{};   // of this solve alone: a tick that finds the grid done has nothing to form
     }
     if (rb == 1)
         HIPCHK(hipMemcpyAsync(g->psi[0], g->psi[1], bytes, hipMemcpyDeviceToDevice, c->stream));

@@ -76,3 +76,23 @@ def test_fp64_batch_matches_alone(kw):
     for g, info, ref in zip(gs, infos, alone):
         _same(info, g.read().cpu().numpy(), ref)
     ctx.close()
+
+
+@pytest.mark.parametrize("tol", [0.5, 2e-3, 1e-9])
+def test_solve_between_ticks_ends_them(tol):
+    """A solve alone leaves its control block as it ended it, however its
+    result came about (formed again behind the test, or before it): a tick
+    that follows finds the grid done, with the solve's counts and field."""
+    torch, lap = need_gpu()
+    ctx = lap.Context(arena_bytes=1 << 30)
+    g = ctx.grid(*_problems(torch)[0], alloc=lap.LAP_ALLOC_FP64)
+    g.set_tol(1e-12)
+    say("solve between ticks", SHAPES[0], tol)
+    done, _ = ctx.batch_step([g], precision="fp64")
+    assert done == [False]
+    ref = g.solve("mg", tol=tol, max_iter=30)
+    u = g.read().cpu().numpy()
+    done, infos = ctx.batch_step([g], precision="fp64")
+    assert done == [True]
+    _same(infos[0], g.read().cpu().numpy(), (ref, u))
+    ctx.close()
