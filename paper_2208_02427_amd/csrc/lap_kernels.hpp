@@ -52,10 +52,13 @@ constexpr int kNormH = 6;
 // decides instead.
 constexpr int kNormWaves = 32768;
 // Grids from kMergedNodes interior nodes on run one pass per cycle over the
-// finest level (merged_ok), whose norms, like those of every other kernel that
-// forms them, belong to this tiling: a halo for four sweeps and the
-// restriction, and as many waves as are resident at once with that pass's
-// registers (two a SIMD).  20 FP64 cycles of 8193^2, without / with a source: 2048
+// finest level (merged_ok), whose norms, like those of every other sweep pass
+// that forms them (and the probe of one), belong to this tiling: a halo for
+// four sweeps and the restriction, and as many waves as are resident at once
+// with that pass's registers (two a SIMD).  The residual kernel, which only
+// reads, keeps the shorter chunks (NORM_RES; see residual_tile); red-black SOR
+// with a test every sweep likes the long ones (12 sweeps of 8193 x 4097 2.63
+// ms, with 32768 waves 2.84).  20 FP64 cycles of 8193^2, without / with a source: 2048
 // waves 11.84 / 14.15 ms, 3072 12.50 / 14.79, 6144 11.92 / 14.29; of 4097^2
 // 4.41 / 5.10, 4.55 / 5.39, 4.53 / 5.27 ms.  The line: one pass against two
 // per cycle 2049^2 2.47 against 2.76 ms, 1537^2 2.17 against 2.35, but 1025^2
@@ -103,12 +106,12 @@ inline int lane_halo(int H, int V) { return H > 2 ? (H + V - 1) / V * V : H; }
 // pre-sweep with norms, residual norms, the FP64 defect correction): the
 // partial sums, and so the stopping decisions, then do not depend on the
 // tuning table or on whether the grid runs alone or inside a batch.
-// Canonical tilings by producer: the stencil passes (sweeps with norms,
-// fused pre-smoothing, residual norms), the FP64 defect correction of the
-// mixed loop, and the fused FP32 post-smoothing + FP64 defect pass (halo of
-// two sweeps and the residual); a norm finalisation reduces the partials of
-// the kind that produced them.
-enum NormKind { NORM_PASS = 0, NORM_DEFECT = 1, NORM_POSTDEF = 2 };
+// Canonical tilings by producer: the sweep passes (sweeps with norms, fused
+// pre-smoothing), the FP64 defect correction of the mixed loop, the fused
+// FP32 post-smoothing + FP64 defect pass (halo of two sweeps and the
+// residual), and the residual kernel; a norm finalisation reduces the
+// partials of the kind that produced them.
+enum NormKind { NORM_PASS = 0, NORM_DEFECT = 1, NORM_POSTDEF = 2, NORM_RES = 3 };
 // The defect pass keeps chunks of >= 64 rows on levels of more than 257
 // rows, >= 16 below.  Grids whose whole FP32 cycle fits one workgroup's LDS
 // (up to ~15k nodes) take this pass at every outer step; in a batch they
@@ -142,7 +145,7 @@ inline Tiling norm_tiling(int m, int n, int kind = NORM_PASS) {
     if (kind == NORM_DEFECT)
         return make_tiling(m, n, kNormDefectV, 0, 16384, 2, n <= kDefectShortRowsN ? 16 : kDefectMinRows);
     if (kind == NORM_POSTDEF) return make_tiling(m, n, 2, 0, 16384, kNormH, n > kPostDefShortRowsN ? 16 : 64);
-    if (merged_size(m, n)) return make_tiling(m, n, kNormPassV, 0, kMergedWaves, kMergedH);
+    if (kind == NORM_PASS && merged_size(m, n)) return make_tiling(m, n, kNormPassV, 0, kMergedWaves, kMergedH);
     return make_tiling(m, n, kNormPassV, 0, kNormWaves, kNormH);
 }
 // Blocks of rows a chunk of the post-smoothing + defect pass may hold.

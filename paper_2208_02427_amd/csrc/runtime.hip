@@ -504,7 +504,8 @@ struct Footprint {
 size_t max_tiles(int m, int n) {
     // the finest tiling any table entry may pick: V = 1, ty = 16
     int t = make_tiling(m, n, 1, 16).ntiles;
-    for (int k : {(int)NORM_PASS, (int)NORM_DEFECT, (int)NORM_POSTDEF}) t = std::max(t, norm_partials(m, n, k));
+    for (int k : {(int)NORM_PASS, (int)NORM_DEFECT, (int)NORM_POSTDEF, (int)NORM_RES})
+        t = std::max(t, norm_partials(m, n, k));
     return (size_t)t;
 }
 
@@ -870,7 +871,7 @@ hipError_t enq_residual_norm(lap_grid* g, int l, const T* u, const T* f) {
     a.cx = (T)c.cx;
     a.cy = (T)c.cy;
     a.d = (T)c.d;
-    a.tl = norm_tiling(L.m, L.n);
+    a.tl = norm_tiling(L.m, L.n, NORM_RES);
     return g->ctx->timed(KC_RESIDUAL, l == 0, (f ? 2.0 : 1.0) * sizeof(T) * nint(L),
                          [&]() { return launch_residual<T>(a, g->ctx->stream); });
 }
@@ -1059,7 +1060,7 @@ int plan_vcycle_zebra(lap_grid* g, HierView<T>& H, int l, const lap_opts& o, boo
     const T* b = H.b[l];
     if (split && head) {
         push_op<T>(ops, KEY_HEAD, OP_RESNORM, l, 0, U, nullptr, b, nullptr, nullptr, 0.0);
-        push_op<T>(ops, KEY_HEAD + 1, OP_FINALIZE, l, 0, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0);
+        push_op<T>(ops, KEY_HEAD + 1, OP_FINALIZE, l, NORM_RES, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0);
     }
     if (!tail) return 0;
     if (l == L - 1) {
@@ -1101,7 +1102,7 @@ int plan_vcycle(lap_grid* g, HierView<T>& H, int l, const lap_opts& o, bool norm
     if (l == L - 1) {
         if (split && head) {
             push_op<T>(ops, KEY_HEAD, OP_RESNORM, l, 0, U[0], nullptr, b, nullptr, nullptr, 0.0);
-            push_op<T>(ops, KEY_HEAD + 1, OP_FINALIZE, l, 0, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0);
+            push_op<T>(ops, KEY_HEAD + 1, OP_FINALIZE, l, NORM_RES, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0);
         }
         if (tail) push_op<T>(ops, KEY_COARSE, OP_COARSE, l, 0, zero_start ? nullptr : U[0], U[0], b, nullptr,
                              nullptr, 0.0);
@@ -1113,7 +1114,7 @@ int plan_vcycle(lap_grid* g, HierView<T>& H, int l, const lap_opts& o, bool norm
     if (split && o.nu1 == 0) {
         if (head) {
             push_op<T>(ops, KEY_HEAD, OP_RESNORM, l, 0, U[0], nullptr, b, nullptr, nullptr, 0.0);
-            push_op<T>(ops, KEY_HEAD + 1, OP_FINALIZE, l, 0, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0);
+            push_op<T>(ops, KEY_HEAD + 1, OP_FINALIZE, l, NORM_RES, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0);
         }
         if (!tail) return 0;
     }
@@ -2161,7 +2162,7 @@ void plan_step(lap_grid* g, const lap_opts& o, int s, int part, std::vector<Op>&
                 // the stopping test of the incoming field, then the full multigrid pass
                 if (part != PART_TAIL) {
                     push_op<double>(ops, KEY_HEAD, OP_RESNORM, 0, 0, g->psi[0], nullptr, g->f64, nullptr, nullptr, 0.0);
-                    push_op<double>(ops, KEY_HEAD + 1, OP_FINALIZE, 0, 0, nullptr, nullptr, nullptr, nullptr,
+                    push_op<double>(ops, KEY_HEAD + 1, OP_FINALIZE, 0, NORM_RES, nullptr, nullptr, nullptr, nullptr,
                                     nullptr, 0.0);
                 }
                 if (part != PART_HEAD) plan_fmg(g, o, ops);
@@ -2197,7 +2198,7 @@ void plan_step(lap_grid* g, const lap_opts& o, int s, int part, std::vector<Op>&
         case LAP_ADI:
             if (part != PART_TAIL) {
                 push_op<double>(ops, KEY_HEAD, OP_RESNORM, 0, 0, g->psi[0], nullptr, g->f64, nullptr, nullptr, 0.0);
-                push_op<double>(ops, KEY_HEAD + 1, OP_FINALIZE, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr,
+                push_op<double>(ops, KEY_HEAD + 1, OP_FINALIZE, 0, NORM_RES, nullptr, nullptr, nullptr, nullptr, nullptr,
                                 0.0);
             }
             if (part != PART_HEAD)
@@ -2806,7 +2807,7 @@ lap_status residual_norms(lap_grid* g, double* l2, double* linf) {
     a.cx = c.cx;
     a.cy = c.cy;
     a.d = c.d;
-    a.tl = norm_tiling(L.m, L.n);
+    a.tl = norm_tiling(L.m, L.n, NORM_RES);
     const double bytes = (g->f64 ? 16.0 : 8.0) * nint(L);   // u (and f) read once
     HIPCHK(g->ctx->timed(KC_RESIDUAL, true, bytes, [&]() { return launch_residual<double>(a, g->ctx->stream); }));
     HIPCHK(launch_finalize(g->partials, a.tl.ntiles, nullptr, g->norm_out, 1, g->ctx->stream));
@@ -3225,7 +3226,7 @@ BatchItem make_item(lap_grid* g, const Op& op, const lap_opts& o, size_t nplan, 
             t = c->tiling(L.m, L.n, KC_RESTRICT, op.dt);
             it.flags = op.flags & SW_RDIFF;
             break;
-        case OP_RESNORM: t = norm_tiling(g->geo[0].m, g->geo[0].n); break;
+        case OP_RESNORM: t = norm_tiling(g->geo[0].m, g->geo[0].n, NORM_RES); break;
         case OP_DEFECT:
             t = norm_tiling(g->geo[0].m, g->geo[0].n, NORM_DEFECT);
             it.e = op.zbuf;   // the FP32 buffer the defect correction sets to zero (zebra cycles)

@@ -533,11 +533,12 @@ __device__ __forceinline__ void restrict_tile(const RestrictArgs<T>& A, int tile
 }
 
 // ------------------------------------------------------------------ residual
-// Rows in the residual kernel's ring (see residual_tile).  8193^2 FP64, the
-// canonical 18-row chunks, HIP events: f = 0 106 us with two rows ahead, 95 us
-// with a ring of 6 (66 registers, 7 waves per SIMD), 99-104 with 8 or 9; with
-// a source 185 -> 178 us.
-constexpr int kResRing = 12;
+// Rows in the residual kernel's ring (see residual_tile).  HIP events, the
+// canonical chunks of 18 rows and less: 8193^2 FP64 f = 0 106 us with two rows
+// ahead, 96 us with a ring of 6 (66 registers, 7 waves per SIMD), 101 with 12
+// (and 114 with 12 on the long chunks of the merged pass); with a source 185,
+// 181 and 188 us.  3000 x 2201 14.7 us with 6, 16.9 with 12; 65^2 8.6 and 9.2.
+constexpr int kResRing = 6;
 
 template <typename T, int V>
 __device__ __forceinline__ void residual_tile(const ResidualArgs<T>& A, int tile, int lane) {
@@ -593,6 +594,11 @@ __device__ __forceinline__ void residual_tile(const ResidualArgs<T>& A, int tile
 }
 
 // ---------------------------------------------------- FP64 defect correction
+// Rows in its ring: one double and one float a row, so more of them fit, and
+// with 64-row chunks a small grid's few wavefronts wait for their loads alone:
+// 1025^2 with a source 33.6 us with a ring of 6, 27.7 with 12.
+constexpr int kDefectRing = 12;
+
 template <int V>
 __device__ __forceinline__ void defect_tile(const DefectArgs& A, int tile, int lane) {
     const int win = tile % A.tl.nwin, chunk = tile / A.tl.nwin;
@@ -605,7 +611,7 @@ __device__ __forceinline__ void defect_tile(const DefectArgs& A, int tile, int l
     // row when the row first enters the stencil (one iteration before it is
     // the centre row), not right after its load, so the loads ahead are not
     // waited for.
-    constexpr int R = kResRing;
+    constexpr int R = kDefectRing;
     double u[R][V], fq[R][V], r[V];
     float ev[R][V], r32[V];
     double s2 = 0.0, mx = 0.0;

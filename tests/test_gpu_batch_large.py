@@ -96,3 +96,31 @@ def test_solve_between_ticks_ends_them(tol):
     assert done == [True]
     _same(infos[0], g.read().cpu().numpy(), (ref, u))
     ctx.close()
+
+
+@pytest.mark.parametrize("kw", [dict(nu1=2, nu2=2), dict(nu1=1, nu2=1), dict(nu1=3, nu2=1), dict(nu1=0, nu2=2),
+                                dict(fmg=True), dict(precision="mixed"), dict(precision="mixed", nu1=1, nu2=1),
+                                dict(method="sor", omega=1.6, check_every=4, max_iter=8),
+                                dict(method="adi", check_every=2, max_iter=4)])
+def test_norms_of_large_grids(kw):
+    """Every pass that forms the norms of a large grid, reduced by the count
+    of its own tiling: the norms of the last test are those of the field it
+    left, computed by the residual kernel (sums of other walks over the same
+    2.4e6 squares: 1e-12 relative holds for any order); alone and in a batch."""
+    torch, lap = need_gpu()
+    kw = dict(dict(method="mg", tol=0.0, max_iter=2), **kw)
+    probs = _problems(torch)[:2]
+    ctx = lap.Context(arena_bytes=2 << 30)
+    say("large norms", kw)
+    for batch in (False, True):
+        if batch and "fmg" in kw:
+            continue
+        gs = [ctx.grid(*p) for p in probs]
+        infos = ctx.solve_batch(gs, **kw) if batch else [g.solve(**kw) for g in gs]
+        for g, info in zip(gs, infos):
+            l2, linf = g.residual()
+            assert info["iterations"] == kw["max_iter"]
+            assert abs(info["res_l2"] - l2) <= 1e-12 * l2
+            assert info["res_linf"] == linf
+            g.destroy()
+    ctx.close()
