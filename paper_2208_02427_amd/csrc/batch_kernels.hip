@@ -125,6 +125,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_resnorm(const BatchItem* items
     }
 }
 
+template <int R>
 __global__ __launch_bounds__(kBlock) void k_batch_defect(const BatchItem* items, const int* tmap, int total) {
     const int nw = gridDim.x * kWavesPerBlock;
     const int lane = threadIdx.x & 63;
@@ -147,7 +148,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_defect(const BatchItem* items,
         A.cy = it.cy;
         A.d = it.d;
         A.tl = item_tiling(it);
-        defect_tile<kNormDefectV>(A, t - it.tile0, lane);   // the canonical defect tiling
+        defect_tile<kNormDefectV, R>(A, t - it.tile0, lane);   // the canonical defect tiling
     }
 }
 
@@ -237,7 +238,12 @@ hipError_t launch_batch(int kind, int dt, int step_flags, const BatchItem* items
                            : launch_batch_t<float>(kind, step_flags, items, tmap, count, total, blocks, s);
         case BK_FINALIZE: k_batch_finalize<<<blocks, kFinBlock, 0, s>>>(items, count); break;
         case BK_RESNORM: k_batch_resnorm<<<blocks, kBlock, 0, s>>>(items, tmap, total); break;
-        case BK_DEFECT: k_batch_defect<<<blocks, kBlock, 0, s>>>(items, tmap, total); break;
+        case BK_DEFECT:
+            if (defect_ring(total) == 6)
+                k_batch_defect<6><<<blocks, kBlock, 0, s>>>(items, tmap, total);
+            else
+                k_batch_defect<12><<<blocks, kBlock, 0, s>>>(items, tmap, total);
+            break;
         case BK_ADI_ROWS:
         case BK_ADI_COLS: return launch_batch_adi(kind, step_flags, dt, items, tmap, total, blocks, s);
         default: return hipErrorInvalidValue;

@@ -118,24 +118,29 @@ hipError_t launch_residual(const ResidualArgs<T>& a, hipStream_t s) {
 template hipError_t launch_residual<double>(const ResidualArgs<double>&, hipStream_t);
 template hipError_t launch_residual<float>(const ResidualArgs<float>&, hipStream_t);
 
-template <int V>
+template <int V, int R>
 __global__ __launch_bounds__(kBlock) void k_defect(DefectArgs A) {
     if (A.ctrl != nullptr && A.ctrl->done) return;
     const int b = xcd_remap(blockIdx.x, gridDim.x);
     const int tile = b * kWavesPerBlock + wave_in_block();
     if (tile >= A.tl.ntiles) return;
-    defect_tile<V>(A, tile, threadIdx.x & 63);
+    defect_tile<V, R>(A, tile, threadIdx.x & 63);
 }
 
-hipError_t launch_defect(const DefectArgs& a, hipStream_t s) {
+template <int R>
+static hipError_t launch_defect_r(const DefectArgs& a, hipStream_t s) {
     const dim3 grid(blocks_for(a.tl)), block(kBlock);
     switch (a.tl.V) {
-        case 1: k_defect<1><<<grid, block, 0, s>>>(a); break;
-        case 2: k_defect<2><<<grid, block, 0, s>>>(a); break;
-        case 4: k_defect<4><<<grid, block, 0, s>>>(a); break;
+        case 1: k_defect<1, R><<<grid, block, 0, s>>>(a); break;
+        case 2: k_defect<2, R><<<grid, block, 0, s>>>(a); break;
+        case 4: k_defect<4, R><<<grid, block, 0, s>>>(a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_defect(const DefectArgs& a, hipStream_t s) {
+    return defect_ring(a.tl.ntiles) == 6 ? launch_defect_r<6>(a, s) : launch_defect_r<12>(a, s);
 }
 
 template <typename T>

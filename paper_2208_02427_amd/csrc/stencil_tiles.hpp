@@ -594,12 +594,16 @@ __device__ __forceinline__ void residual_tile(const ResidualArgs<T>& A, int tile
 }
 
 // ---------------------------------------------------- FP64 defect correction
-// Rows in its ring: one double and one float a row, so more of them fit, and
-// with 64-row chunks a small grid's few wavefronts wait for their loads alone:
-// 1025^2 with a source 33.6 us with a ring of 6, 27.7 with 12.
-constexpr int kDefectRing = 12;
+// Rows in its ring.  Up to a few waves a SIMD a wavefront waits for its own
+// loads, and more rows in flight help; from about three a SIMD on the
+// others' loads fill its waits and the longer ring costs more than it gives;
+// a launch of many rounds gains again.  6 / 12 rows, HIP events, with a source:
+// 1025^2 (288 waves) 33.6 / 27.7 us, 3073^2 (2496) 70.2 / 65.9, 200 merged grids
+// of 33..257 (3348) 21.9 / 24.0, 4097^2 (4416) 118 / 126, 6145^2 (9888) 259 /
+// 254, 8193^2 (16166) 454 / 442.
+inline int defect_ring(int waves) { return waves >= 3072 && waves < 8192 ? 6 : 12; }
 
-template <int V>
+template <int V, int R>
 __device__ __forceinline__ void defect_tile(const DefectArgs& A, int tile, int lane) {
     const int win = tile % A.tl.nwin, chunk = tile / A.tl.nwin;
     const Cols<V> c(win, lane, A.m, A.P, A.tl.H);
@@ -611,7 +615,6 @@ __device__ __forceinline__ void defect_tile(const DefectArgs& A, int tile, int l
     // row when the row first enters the stencil (one iteration before it is
     // the centre row), not right after its load, so the loads ahead are not
     // waited for.
-    constexpr int R = kDefectRing;
     double u[R][V], fq[R][V], r[V];
     float ev[R][V], r32[V];
     double s2 = 0.0, mx = 0.0;

@@ -124,3 +124,26 @@ def test_norms_of_large_grids(kw):
             assert info["res_linf"] == linf
             g.destroy()
     ctx.close()
+
+
+def test_defect_correction_rings_bitwise():
+    """The FP64 defect correction's row ring follows the launch's wavefronts:
+    1120 alone (12 rows), 3360 in a batch of three (6 rows)."""
+    torch, lap = need_gpu()
+    m = n = 2049
+    kw = dict(method="mg", precision="mixed", nu1=1, nu2=1, tol=0.0, max_iter=3)
+    ctx = lap.Context(arena_bytes=2 << 30)
+    gs, alone = [], []
+    for k in range(3):
+        psi, f, dx, dy = rand_problem(m, n, seed=60 + k, source=k != 1)
+        p = to_dev(torch, psi)
+        g = ctx.grid(p, to_dev(torch, f) if f is not None else None, dx, dy, alloc=lap.LAP_ALLOC_MIXED)
+        say("defect ring alone", m, n, k)
+        alone.append((g.solve(**kw), g.read().cpu().numpy()))
+        g.write(p)
+        gs.append(g)
+    say("defect ring batch")
+    infos = ctx.solve_batch(gs, **kw)
+    for g, info, ref in zip(gs, infos, alone):
+        _same(info, g.read().cpu().numpy(), ref)
+    ctx.close()
