@@ -11,12 +11,14 @@
 // serial chain of operations with no bandwidth to speak of, so they run in
 // ONE wavefront (LDS accesses of a wavefront are in order and its barriers
 // are free; sixteen wavefronts spent most of their time meeting at barriers),
-// and what is not on the chain is taken off it.
+// and what is not on the chain is taken off it.  A residual as the monitored
+// quantity is no chain: further wavefronts wait through the sweep and form it
+// with the first (paper_residual).
 //
 // Order.  Lexicographic SOR updates node (i, j) after (i-1, j) and (i, j-1)
 // and before (i+1, j) and (i, j+1).  All nodes of one anti-diagonal i + j = d
 // depend only on diagonals d - 1 (already new) and d + 1 (still old), so the
-// workgroup updates a diagonal at once and moves to the next after a barrier:
+// wavefront updates a diagonal at once and moves to the next:
 // every node sees exactly the operands of the row-by-row loop.  The line
 // methods solve one line after another (each line's Thomas recurrence is
 // sequential; its right-hand side and its relaxation are computed by all
@@ -32,12 +34,15 @@
 // paper's order, w = 1.3, 6.66 ms with 1024 threads and the divisions on the
 // chain, 3.12 ms now.  Bound by the latency of the chain's dependent FP64
 // operations: four per unknown forwards, two backwards.
+#include <algorithm>
 #include <cmath>
 
 #include "lap_kernels.hpp"
 #include "../../include/lap.h"
 
 namespace lap {
+
+constexpr int kPaperRed = 16;   // reduction slots: wavefronts of 1024 lanes
 
 __device__ __forceinline__ double block_max(double v, double* red) {
 #pragma unroll
@@ -52,19 +57,12 @@ __device__ __forceinline__ double block_max(double v, double* red) {
     return r;
 }
 
-// Sum over the workgroup: per-thread partials in index order, then the
-// wavefront sums in wave order (fixed for a given grid and block size).
-__device__ __forceinline__ double block_sum(double v, double* red) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[w] = v;
-    __syncthreads();
-    double r = red[0];
-    for (int k = 1; k < nw; ++k) r = r + red[k];
-    __syncthreads();
-    return r;
+// Order between the lanes of the one wavefront that sweeps: its LDS accesses
+// are in order, only the compiler must keep them so.
+__device__ __forceinline__ void paper_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // A line system of K unknowns (row line: along i; column line: along j) and
@@ -162,7 +160,7 @@ __device__ double paper_line(const PaperArgs& A, double* u, double* u0, int line
     const int K = g.K;
     const double d = A.d, a = F.a;
     paper_rhs(A, g, u, rhs);
-    __syncthreads();
+    paper_sync();
     constexpr int B = 8;
     if (threadIdx.x == 0) {
         double q = 0.0;
@@ -192,14 +190,14 @@ __device__ double paper_line(const PaperArgs& A, double* u, double* u0, int line
             chain(r1, y1, k + B);
         }
     }
-    __syncthreads();
+    paper_sync();
     bool same = true;
     for (int k = threadIdx.x; k < K; k += 64) {
         const double piv = k == 0 ? d : d - a * F.cp[k - 1];
         same = same && __double_as_longlong(xq[k].x / piv) == __double_as_longlong(xq[k].y);
     }
     if (__any(!same)) {
-        __syncthreads();
+        paper_sync();
         if (threadIdx.x == 0) {
             double q = 0.0;
             for (int k = 0; k < K; ++k) {
@@ -209,7 +207,7 @@ __device__ double paper_line(const PaperArgs& A, double* u, double* u0, int line
             }
         }
     }
-    __syncthreads();
+    paper_sync();
     if (threadIdx.x == 0) {
         // x_k = rp_k - c'_k x_{k+1}, in groups of eight from the top; the first
         // group holds the steps beyond the line's end
@@ -246,9 +244,9 @@ __device__ double paper_line(const PaperArgs& A, double* u, double* u0, int line
             chain(r0, c0, k - B);
         }
     }
-    __syncthreads();
+    paper_sync();
     const double mx = paper_relax<KEEP>(A, g, u, u0, rhs);
-    __syncthreads();
+    paper_sync();
     return mx;
 }
 
@@ -259,7 +257,7 @@ __device__ double paper_line_plain(const PaperArgs& A, double* u, double* u0, in
                                    double* rhs, double* cp, double* rp) {
     const PaperLine g(A, line, dir);
     paper_rhs(A, g, u, rhs);
-    __syncthreads();
+    paper_sync();
     if (threadIdx.x == 0) {
         const double b = A.d;
         cp[0] = a / b;
@@ -272,72 +270,91 @@ __device__ double paper_line_plain(const PaperArgs& A, double* u, double* u0, in
         rhs[g.K - 1] = rp[g.K - 1];
         for (int k = g.K - 2; k >= 0; --k) rhs[k] = rp[k] - cp[k] * rhs[k + 1];
     }
-    __syncthreads();
+    paper_sync();
     const double mx = paper_relax<KEEP>(A, g, u, u0, rhs);
-    __syncthreads();
+    paper_sync();
     return mx;
+}
+
+// Residual norms of u over the workgroup: max |r| (SUM: sum r^2).  The sum is
+// that of 1024 lanes, lane t adding nodes t, t + 1024, ... in order, then a
+// butterfly per 64 lanes and the results in order, whatever number of
+// threads forms it: the monitored values do not depend on the launch.  By the
+// sweep's wavefront alone it is N / 64 turns of one wave: 30 iterations of
+// lexicographic SOR on 97 x 97 took 2.92 ms, with 16 wavefronts 2.07 (2.01
+// with the largest update, which comes with the sweep, as the rule).
+constexpr int kPaperLanes = 1024;
+template <bool SUM>
+__device__ double paper_residual(const PaperArgs& A, const double* u, double* red) {
+    const int m = A.m, mi = m - 2, N = mi * (A.n - 2), nt = blockDim.x;
+    const float inv = 1.0f / (float)mi;
+    const auto res = [&](int q) {
+        const int jj = seg_div(q, inv), i = 1 + q - jj * mi, j = 1 + jj;
+        const int p = j * m + i;
+        const double Lu = (A.cx * (u[p - 1] + u[p + 1]) + A.cy * (u[p - m] + u[p + m])) - A.d * u[p];
+        return (A.f != nullptr ? A.f[(size_t)j * A.P + i] : 0.0) - Lu;
+    };
+    if constexpr (!SUM) {
+        double mx = 0.0;
+        for (int q = threadIdx.x; q < N; q += nt) mx = fmax(mx, fabs(res(q)));
+        return block_max(mx, red);
+    }
+    for (int v = 0; v < N && v < kPaperLanes; v += nt) {
+        double s2 = 0.0;
+        for (int q = v + (int)threadIdx.x; q < N; q += kPaperLanes) {
+            const double r = res(q);
+            s2 = s2 + r * r;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s2 += __shfl_xor(s2, o);
+        if ((threadIdx.x & 63) == 0) red[(v + (int)threadIdx.x) >> 6] = s2;
+    }
+    __syncthreads();
+    double s = red[0];
+    for (int k = 1; k < min((N + 63) >> 6, kPaperRed); ++k) s = s + red[k];
+    __syncthreads();
+    return s;
 }
 
 // The monitored quantity of the stopping rule after an iteration: the
 // largest update max|psi - psi_start| (Eq. (16); mx, the thread's largest,
 // taken where the nodes were updated), max|r| or ||r||_2 / ||r_0||_2.
 __device__ double paper_monitor(const PaperArgs& A, const double* u, double mx, double r0, double* red) {
-    const int m = A.m, n = A.n, N = (m - 2) * (n - 2);
     if (A.stop == LAP_STOP_DELTA) return block_max(mx, red);
-    double rmx = 0.0, s2 = 0.0;
-    for (int q = threadIdx.x; q < N; q += blockDim.x) {
-        const int i = 1 + q % (m - 2), j = 1 + q / (m - 2);
-        const int p = j * m + i;
-        const double Lu = (A.cx * (u[p - 1] + u[p + 1]) + A.cy * (u[p - m] + u[p + m])) - A.d * u[p];
-        const double r = (A.f != nullptr ? A.f[(size_t)j * A.P + i] : 0.0) - Lu;
-        rmx = fmax(rmx, fabs(r));
-        s2 = s2 + r * r;
-    }
     if (A.stop == LAP_STOP_REL_L2) {
-        const double s = block_sum(s2, red);
+        const double s = paper_residual<true>(A, u, red);
         return r0 > 0.0 ? sqrt(s) / r0 : 0.0;
     }
-    return block_max(rmx, red);
+    return paper_residual<false>(A, u, red);
 }
 
 // LDS (doubles): reduction slots (16), for the line methods their scratch and
 // factors (tables: 9 (max(m, n) + kPaperPad), rounded up to pairs; else 3
 // max(m, n) of scratch alone), u (n x m, row stride m) and a second field
 // (Jacobi: the other iterate; ADI: the values at the start of the iteration).
-constexpr int kPaperRed = 16;
 __host__ __device__ constexpr int paper_pad(int m, int n) { return ((m > n ? m : n) + kPaperPad + 1) / 2 * 2; }
 __host__ __device__ constexpr int paper_scratch(int m, int n, bool lines, bool tables) {
     return lines ? (tables ? 9 * paper_pad(m, n) : 3 * (m > n ? m : n)) : 0;
 }
 
-// NT: 64 for the sequential methods.
-template <int NT>
+// NT: the largest workgroup.  The sequential methods sweep in its first
+// wavefront, the others meet it at the monitor.
+template <int NT, bool LINES>
 __global__ __launch_bounds__(NT) void k_paper(PaperArgs A, int tables) {
     extern __shared__ double2 lds2[];
     double* lds = reinterpret_cast<double*>(lds2);
-    const int m = A.m, n = A.n, N = (m - 2) * (n - 2);
-    const bool lines = A.method == LAP_SLOR_LEX || A.method == LAP_ADI_LEX;
+    const int m = A.m, n = A.n, N = (m - 2) * (n - 2), nt = blockDim.x;
     double* red = lds;
     double* sc = lds + kPaperRed;
-    double* u = sc + paper_scratch(m, n, lines, tables != 0);
+    double* u = sc + paper_scratch(m, n, LINES, tables != 0);
     double* u0 = u + (size_t)m * n;
-    for (int q = threadIdx.x; q < m * n; q += NT) {
+    for (int q = threadIdx.x; q < m * n; q += nt) {
         const int i = q % m, j = q / m;
         u0[q] = u[q] = A.u[(size_t)j * A.P + i];
     }
     __syncthreads();
     double r0 = 0.0;
-    if (A.stop == LAP_STOP_REL_L2) {
-        double s2 = 0.0;
-        for (int q = threadIdx.x; q < N; q += NT) {
-            const int i = 1 + q % (m - 2), j = 1 + q / (m - 2);
-            const int p = j * m + i;
-            const double Lu = (A.cx * (u[p - 1] + u[p + 1]) + A.cy * (u[p - m] + u[p + m])) - A.d * u[p];
-            const double r = (A.f != nullptr ? A.f[(size_t)j * A.P + i] : 0.0) - Lu;
-            s2 = s2 + r * r;
-        }
-        r0 = sqrt(block_sum(s2, red));
-    }
+    if (A.stop == LAP_STOP_REL_L2) r0 = sqrt(paper_residual<true>(A, u, red));
     const double cx = A.cx, cy = A.cy, inv_d = A.inv_d, w = A.omega;
     // the line systems: a x_{k-1} + d x_k + a x_{k+1} = r_k, a = -c (-w c inside)
     const int L = paper_pad(m, n), Lp = m > n ? m : n;
@@ -350,7 +367,7 @@ __global__ __launch_bounds__(NT) void k_paper(PaperArgs A, int tables) {
     double* rhs = sc + 6 * L;
     Fx.cp = rhs + L;
     Fy.cp = rhs + 2 * L;
-    if (lines && tables) {
+    if (LINES && tables) {
         // the two directions' chains of divisions side by side (a lane each)
         const bool y = threadIdx.x == 1;
         PaperFactor F;
@@ -364,10 +381,26 @@ __global__ __launch_bounds__(NT) void k_paper(PaperArgs A, int tables) {
     double q = 0.0;
     while (it < A.max_iter) {
         double mx = 0.0;
-        if (A.method == LAP_JACOBI) {
+        if constexpr (LINES) {
+            // SLOR: rows j = 1..n-2; ADI: the rows, then columns i = 1..m-2
+            const bool adi = A.method == LAP_ADI_LEX;
+            if (threadIdx.x < 64) {
+                for (int j = 1; j <= n - 2; ++j) {
+                    double* const keep = adi ? u0 : nullptr;
+                    mx = fmax(mx, tables ? paper_line<true>(A, u, keep, j, 0, Fx, rhs, xq)
+                                         : paper_line_plain<true>(A, u, keep, j, 0, Fx.a, sc, sc + Lp, sc + 2 * Lp));
+                }
+                if (adi) {
+                    mx = 0.0;
+                    for (int i = 1; i <= m - 2; ++i)
+                        mx = fmax(mx, tables ? paper_line<false>(A, u, u0, i, 1, Fy, rhs, xq)
+                                             : paper_line_plain<false>(A, u, u0, i, 1, Fy.a, sc, sc + Lp, sc + 2 * Lp));
+                }
+            }
+        } else if (A.method == LAP_JACOBI) {
             // every node from the values at the start of the iteration
             double* t = u0; u0 = u; u = t;
-            for (int k = threadIdx.x; k < N; k += NT) {
+            for (int k = threadIdx.x; k < N; k += nt) {
                 const int i = 1 + k % (m - 2), j = 1 + k / (m - 2);
                 const int p = j * m + i;
                 const double fv = A.f != nullptr ? A.f[(size_t)j * A.P + i] : 0.0;
@@ -375,39 +408,26 @@ __global__ __launch_bounds__(NT) void k_paper(PaperArgs A, int tables) {
                 u[p] = v;
                 mx = fmax(mx, fabs(v - u0[p]));
             }
-            __syncthreads();
-        } else if (A.method == LAP_SOR_LEX) {
-            // anti-diagonals d = i + j in increasing order
+        } else if (threadIdx.x < 64) {
+            // lexicographic SOR: anti-diagonals d = i + j in increasing order; node (i, d - i)
+            // lies at d m - i (m - 1), a scalar and a constant of the lane
+            const int lane = threadIdx.x, um = 1 - m, fm = 1 - A.P;
             for (int dg = 2; dg <= (m - 2) + (n - 2); ++dg) {
                 const int ilo = dg - (n - 2) > 1 ? dg - (n - 2) : 1;
                 const int ihi = dg - 1 < m - 2 ? dg - 1 : m - 2;
-                for (int i = ilo + (int)threadIdx.x; i <= ihi; i += NT) {
-                    const int j = dg - i;
-                    const int p = j * m + i;
-                    const double fv = A.f != nullptr ? A.f[(size_t)j * A.P + i] : 0.0;
+                int p = (dg - ilo) * m + ilo + lane * um, fp = (dg - ilo) * A.P + ilo + lane * fm;
+                for (int i = ilo + lane; i <= ihi; i += 64, p += 64 * um, fp += 64 * fm) {
+                    const double fv = A.f != nullptr ? A.f[fp] : 0.0;
                     const double old = u[p];
                     const double t = ((cx * (u[p - 1] + u[p + 1]) + cy * (u[p - m] + u[p + m])) - fv) * inv_d;
                     const double v = old + w * (t - old);
                     u[p] = v;
                     mx = fmax(mx, fabs(v - old));
                 }
-                __syncthreads();
-            }
-        } else {
-            // SLOR: rows j = 1..n-2; ADI: the rows, then columns i = 1..m-2
-            const bool adi = A.method == LAP_ADI_LEX;
-            for (int j = 1; j <= n - 2; ++j) {
-                double* const keep = adi ? u0 : nullptr;
-                mx = fmax(mx, tables ? paper_line<true>(A, u, keep, j, 0, Fx, rhs, xq)
-                                     : paper_line_plain<true>(A, u, keep, j, 0, Fx.a, sc, sc + Lp, sc + 2 * Lp));
-            }
-            if (adi) {
-                mx = 0.0;
-                for (int i = 1; i <= m - 2; ++i)
-                    mx = fmax(mx, tables ? paper_line<false>(A, u, u0, i, 1, Fy, rhs, xq)
-                                         : paper_line_plain<false>(A, u, u0, i, 1, Fy.a, sc, sc + Lp, sc + 2 * Lp));
+                paper_sync();
             }
         }
+        __syncthreads();
         ++it;
         q = paper_monitor(A, u, mx, r0, red);
         if (!isfinite(q) || q > 1e30) {
@@ -420,7 +440,7 @@ __global__ __launch_bounds__(NT) void k_paper(PaperArgs A, int tables) {
             break;
         }
     }
-    for (int p = threadIdx.x; p < m * n; p += NT) {
+    for (int p = threadIdx.x; p < m * n; p += nt) {
         const int i = p % m, j = p / m;
         A.u[(size_t)j * A.P + i] = u[p];
     }
@@ -440,7 +460,8 @@ size_t paper_lds_bytes(int m, int n) {
 }
 
 hipError_t paper_set_lds_limit(int bytes) {
-    for (const void* f : {(const void*)k_paper<64>, (const void*)k_paper<256>, (const void*)k_paper<1024>}) {
+    for (const void* f : {(const void*)k_paper<64, true>, (const void*)k_paper<256, true>, (const void*)k_paper<64, false>,
+                          (const void*)k_paper<1024, false>}) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e != hipSuccess) return e;
     }
@@ -454,12 +475,24 @@ hipError_t launch_paper(const PaperArgs& a, int lds_max, hipStream_t s) {
     };
     const bool tables = need(true) <= (size_t)lds_max;
     const size_t bytes = need(tables);
-    if (a.method != LAP_JACOBI)
-        k_paper<64><<<1, 64, bytes, s>>>(a, tables ? 1 : 0);
-    else if ((a.m - 2) * (a.n - 2) <= 1024)   // one to four nodes a thread, four wavefronts to a barrier
-        k_paper<256><<<1, 256, bytes, s>>>(a, 0);
+    const int N = (a.m - 2) * (a.n - 2);
+    const bool residual = a.stop != LAP_STOP_DELTA;
+    if (lines) {
+        // four wavefronts for the monitor: with more, the chain's registers would be cut
+        if (residual && N > 64)
+            k_paper<256, true><<<1, 256, bytes, s>>>(a, tables ? 1 : 0);
+        else
+            k_paper<64, true><<<1, 64, bytes, s>>>(a, tables ? 1 : 0);
+        return hipGetLastError();
+    }
+    // Jacobi: one to four nodes a thread, four wavefronts to a barrier, or sixteen wavefronts;
+    // SOR by diagonals: a wavefront, and a node a thread for a residual
+    int threads = a.method == LAP_JACOBI ? (N <= 1024 ? 256 : 1024) : 64;
+    if (residual) threads = std::min(kPaperLanes, (N + 63) / 64 * 64);
+    if (threads == 64)
+        k_paper<64, false><<<1, 64, bytes, s>>>(a, 0);
     else
-        k_paper<1024><<<1, 1024, bytes, s>>>(a, 0);
+        k_paper<1024, false><<<1, threads, bytes, s>>>(a, 0);
     return hipGetLastError();
 }
 
