@@ -267,14 +267,17 @@ hipError_t launch_write_field(const double* src, double* d0, double* d1, int m, 
 
 // Pitched field -> dense (m-pitched) field.  A thread keeps four loads in
 // flight; the dense rows are nontemporal (nothing here reads them again).
-// 8193^2: 365 us as the runtime's two-dimensional copy.
+// 8193^2: 365 us as the runtime's two-dimensional copy.  Grids of few rows
+// split them over the launch's second dimension (kReadBlocks workgroups in
+// all): with a workgroup a row 100000 x 9 took 52 us a call, the copy 43.
+constexpr int kReadBlocks = 2048;
 __global__ __launch_bounds__(kBlock) void k_read_field(const double* __restrict__ src, double* __restrict__ dst, int m,
                                                        int n, int P) {
     for (int j = blockIdx.x; j < n; j += gridDim.x) {
         const double* s = src + (size_t)j * P;
         double* d = dst + (size_t)j * m;
         constexpr int U = 4;
-        for (int i0 = threadIdx.x; i0 < m; i0 += U * kBlock) {
+        for (int i0 = blockIdx.y * U * kBlock + threadIdx.x; i0 < m; i0 += gridDim.y * U * kBlock) {
             double v[U];
 #pragma unroll
             for (int k = 0; k < U; ++k) v[k] = i0 + k * kBlock < m ? s[i0 + k * kBlock] : 0.0;
@@ -287,7 +290,8 @@ __global__ __launch_bounds__(kBlock) void k_read_field(const double* __restrict_
 
 hipError_t launch_read_field(const double* src, double* dst, int m, int n, int P, hipStream_t s) {
     if (m <= 0 || n <= 0) return hipSuccess;
-    k_read_field<<<std::min(n, 16384), kBlock, 0, s>>>(src, dst, m, n, P);
+    const int rows = std::min(n, 16384), parts = (m + 4 * kBlock - 1) / (4 * kBlock);
+    k_read_field<<<dim3(rows, std::min(parts, std::max(1, kReadBlocks / rows))), kBlock, 0, s>>>(src, dst, m, n, P);
     return hipGetLastError();
 }
 
