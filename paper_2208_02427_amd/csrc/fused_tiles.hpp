@@ -120,6 +120,7 @@ struct FusedLane {
     bool st;             // it stores its columns (it holds an output column)
     bool cst[V];         // element e is an even output column (full weighting)
     bool cout[V];        // element e is an output column
+    bool cint[V];        // element e is an interior column
     bool iodd;           // V == 1: the column is odd
     T w[2][V];           // relaxation by row parity (OmegaMask)
 };
@@ -249,12 +250,14 @@ __device__ __forceinline__ void fused_step(const SweepArgs<T>& A, FusedRegs<T, V
     const int q = j + 1 - 2 * NS;
     T(&o)[V] = R.u[ring_slot<K>(PH, 1 - 2 * NS)];
     if constexpr ((FL & SW_DEF) != 0) {
-        // o is row q of the final correction: psi_out = psi_in + e there, and
-        // the FP64 residual of the updated iterate at row q - 1
+        // o is row q of the final correction: psi_out = psi_in + e there (the
+        // perimeter stays, also beside a correction that overflowed: its own
+        // value in o, weighted by zero, is then no number), and the FP64
+        // residual of the updated iterate at row q - 1
         constexpr int DQ = 1 - 2 * NS;
         double(&pn)[V] = R.psi[ring_slot<KD>(PH, DQ)];
 #pragma unroll
-        for (int e = 0; e < V; ++e) pn[e] = pn[e] + (double)o[e];
+        for (int e = 0; e < V; ++e) pn[e] = pn[e] + (double)(l.cint[e] ? o[e] : T(0));
         if (q >= j0 && q <= j1 && l.st) st_lane<double, V, NT>(A.psi_out + (ptrdiff_t)q * A.Ps, pn, l.off64);
         if (q - 1 >= j0 && q - 1 <= j1) {
             const double(&pc)[V] = R.psi[ring_slot<KD>(PH, DQ - 1)];
@@ -460,6 +463,7 @@ __device__ __forceinline__ void fused_tile(const SweepArgs<T>& A0, int tile, int
         for (int e = 0; e < V; ++e) {
             l.st = l.st || c.cout[e];
             l.cout[e] = c.cout[e];
+            l.cint[e] = c.cint[e];
             l.cst[e] = c.cout[e] && ((c.i0 + e) & 1) == 0;
             l.w[0][e] = wm.w[0][e];
             l.w[1][e] = wm.w[1][e];
