@@ -239,6 +239,22 @@ struct SweepArgs {
     int rowpart, rp_off;
 };
 
+// Whether a fused pass with these flags has every array that it reads or
+// writes: its loads are unconditional, so the host must not let a launch
+// without one through (psi, rhs: SW_DEF's iterate, update and right-hand side).
+inline bool fused_arrays(int flags, const void* uin, const void* uout, const void* f, const void* ec, const void* bc,
+                         const void* partials, const void* psi_in = nullptr, const void* psi_out = nullptr,
+                         const void* rhs_out = nullptr) {
+    const bool def = (flags & SW_DEF) != 0, probe = (flags & SW_PROBE) != 0;
+    if (!(flags & SW_ZERO) && uin == nullptr) return false;
+    if ((flags & SW_F) && f == nullptr) return false;
+    if ((flags & SW_PROLONG) && ec == nullptr) return false;
+    if ((flags & SW_RESTRICT) && !probe && bc == nullptr) return false;
+    if ((flags & (SW_NORM | SW_DEF)) && partials == nullptr) return false;
+    if (def) return psi_in != nullptr && psi_out != nullptr && rhs_out != nullptr;
+    return probe || uout != nullptr;
+}
+
 template <typename T>
 struct RestrictArgs {
     const T* u;

@@ -3407,6 +3407,11 @@ lap_status get_plan(lap_ctx* c, const std::vector<lap_grid*>& gs, const std::vec
                 delete p;
                 return fail(LAP_EINVAL, "internal error: a norm item without its canonical tiling or input");
             }
+            if (go.second.kind == OP_SWEEP && is_fused(go.second.flags) &&
+                !fused_arrays(go.second.flags, it.in, it.out, it.f, it.ec, it.bc, it.partials)) {
+                delete p;
+                return fail(LAP_EINVAL, "internal error: a fused pass without one of its arrays");
+            }
             sub[std::make_tuple(go.second.kind, go.second.dt, go.second.flags & ~SW_F, vkey)].push_back({go, it});
         }
         for (auto& skv : sub) {
