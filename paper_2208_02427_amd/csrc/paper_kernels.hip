@@ -58,8 +58,13 @@ __device__ __forceinline__ double block_max(double v, double* red) {
 }
 
 // Order between the lanes of the one wavefront that sweeps: its LDS accesses
-// are in order, only the compiler must keep them so.
+// are in order, only the compiler must keep them so.  NT: the largest workgroup.
+template <int NT>
 __device__ __forceinline__ void paper_sync() {
+    if constexpr (NT == 64) {
+        __syncthreads();
+        return;
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -153,14 +158,14 @@ __device__ void paper_factor(const PaperFactor& F, double d, int K) {
 // overflow, vanish or are not numbers), the line's recurrence is run again
 // with divisions.  The values are those of the plain recurrence either way.
 // The operands of the next eight steps are read while eight are computed.
-template <bool KEEP>
+template <bool KEEP, int NT>
 __device__ double paper_line(const PaperArgs& A, double* u, double* u0, int line, int dir, const PaperFactor& F,
                              double* rhs, double2* xq) {
     const PaperLine g(A, line, dir);
     const int K = g.K;
     const double d = A.d, a = F.a;
     paper_rhs(A, g, u, rhs);
-    paper_sync();
+    paper_sync<NT>();
     constexpr int B = 8;
     if (threadIdx.x == 0) {
         double q = 0.0;
@@ -190,14 +195,14 @@ __device__ double paper_line(const PaperArgs& A, double* u, double* u0, int line
             chain(r1, y1, k + B);
         }
     }
-    paper_sync();
+    paper_sync<NT>();
     bool same = true;
     for (int k = threadIdx.x; k < K; k += 64) {
         const double piv = k == 0 ? d : d - a * F.cp[k - 1];
         same = same && __double_as_longlong(xq[k].x / piv) == __double_as_longlong(xq[k].y);
     }
     if (__any(!same)) {
-        paper_sync();
+        paper_sync<NT>();
         if (threadIdx.x == 0) {
             double q = 0.0;
             for (int k = 0; k < K; ++k) {
@@ -207,7 +212,7 @@ __device__ double paper_line(const PaperArgs& A, double* u, double* u0, int line
             }
         }
     }
-    paper_sync();
+    paper_sync<NT>();
     if (threadIdx.x == 0) {
         // x_k = rp_k - c'_k x_{k+1}, in groups of eight from the top; the first
         // group holds the steps beyond the line's end
@@ -244,20 +249,20 @@ __device__ double paper_line(const PaperArgs& A, double* u, double* u0, int line
             chain(r0, c0, k - B);
         }
     }
-    paper_sync();
+    paper_sync<NT>();
     const double mx = paper_relax<KEEP>(A, g, u, u0, rhs);
-    paper_sync();
+    paper_sync<NT>();
     return mx;
 }
 
 // The same for a grid that leaves no room for the factors: the plain
 // recurrence with its divisions.  rhs, cp, rp: K values each.
-template <bool KEEP>
+template <bool KEEP, int NT>
 __device__ double paper_line_plain(const PaperArgs& A, double* u, double* u0, int line, int dir, double a,
                                    double* rhs, double* cp, double* rp) {
     const PaperLine g(A, line, dir);
     paper_rhs(A, g, u, rhs);
-    paper_sync();
+    paper_sync<NT>();
     if (threadIdx.x == 0) {
         const double b = A.d;
         cp[0] = a / b;
@@ -270,9 +275,9 @@ __device__ double paper_line_plain(const PaperArgs& A, double* u, double* u0, in
         rhs[g.K - 1] = rp[g.K - 1];
         for (int k = g.K - 2; k >= 0; --k) rhs[k] = rp[k] - cp[k] * rhs[k + 1];
     }
-    paper_sync();
+    paper_sync<NT>();
     const double mx = paper_relax<KEEP>(A, g, u, u0, rhs);
-    paper_sync();
+    paper_sync<NT>();
     return mx;
 }
 
@@ -387,14 +392,14 @@ __global__ __launch_bounds__(NT) void k_paper(PaperArgs A, int tables) {
             if (threadIdx.x < 64) {
                 for (int j = 1; j <= n - 2; ++j) {
                     double* const keep = adi ? u0 : nullptr;
-                    mx = fmax(mx, tables ? paper_line<true>(A, u, keep, j, 0, Fx, rhs, xq)
-                                         : paper_line_plain<true>(A, u, keep, j, 0, Fx.a, sc, sc + Lp, sc + 2 * Lp));
+                    mx = fmax(mx, tables ? paper_line<true, NT>(A, u, keep, j, 0, Fx, rhs, xq)
+                                         : paper_line_plain<true, NT>(A, u, keep, j, 0, Fx.a, sc, sc + Lp, sc + 2 * Lp));
                 }
                 if (adi) {
                     mx = 0.0;
                     for (int i = 1; i <= m - 2; ++i)
-                        mx = fmax(mx, tables ? paper_line<false>(A, u, u0, i, 1, Fy, rhs, xq)
-                                             : paper_line_plain<false>(A, u, u0, i, 1, Fy.a, sc, sc + Lp, sc + 2 * Lp));
+                        mx = fmax(mx, tables ? paper_line<false, NT>(A, u, u0, i, 1, Fy, rhs, xq)
+                                             : paper_line_plain<false, NT>(A, u, u0, i, 1, Fy.a, sc, sc + Lp, sc + 2 * Lp));
                 }
             }
         } else if (A.method == LAP_JACOBI) {
@@ -424,7 +429,7 @@ __global__ __launch_bounds__(NT) void k_paper(PaperArgs A, int tables) {
                     u[p] = v;
                     mx = fmax(mx, fabs(v - old));
                 }
-                paper_sync();
+                paper_sync<NT>();
             }
         }
         __syncthreads();
