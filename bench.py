@@ -64,7 +64,7 @@ BATCH_INNER_MARGIN = 0.03
 # with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by the counts of a
 # 1 GiB stream copy (summaries under profiles/); keyed by kernel class and the
 # tiling (V, ty, target waves) they were taken with, for this kernel version.
-FINE_TRAFFIC = {("pre", 2, 0, 32768): 1.2863e9, ("two", 2, 0, 3072): 1.2285e9}
+FINE_TRAFFIC = {("cycle", 2, 0, 2048): 1.3806e9, ("pre", 2, 0, 2048): 1.2309e9, ("two", 2, 0, 3072): 1.2400e9}
 
 # kernel classes timed on the finest level (numbering of lap.h)
 FINE_CLASSES = {"sweep": 0, "sweep_prolong": 1, "restrict": 2, "pre": 10, "two": 11, "cycle": 14}

@@ -181,7 +181,9 @@ lap_status lap_ctx_usage(lap_ctx* ctx, size_t* used, size_t* largest_free);
  * with fused prolongation, 2 residual + full weighting, 3 defect correction
  * (FP64), 4 coarse solve, 5 norm finalise, 6 ADI row lines, 7 ADI column
  * lines, 8 residual, 9 small-level subtree (one launch per sub-V-cycle; its
- * bytes are the top level's right-hand side read and result written),
+ * bytes are the top level's right-hand side read and result written; also the
+ * small levels of a zebra cycle in one launch, and whole FP64 solves of grids
+ * that fit one workgroup),
  * 10 fused pre-smoothing pass (one or two sweeps + residual + full
  * weighting), 11 fused two-sweep pass with the prolongation (post-smoothing),
  * 12 fused two-sweep pass without a transfer (red-black SOR, further
@@ -189,9 +191,10 @@ lap_status lap_ctx_usage(lap_ctx* ctx, size_t* used, size_t* largest_free);
  * (LAP_JACOBI .. LAP_ADI_LEX; no algorithmic bytes), 14 fused four-sweep pass
  * (a mixed step's FP32 cycle: the level-0 post-smoothing after the bilinear
  * correction, then the next cycle's pre-smoothing, residual and full
- * weighting; in FP64 four sweeps of red-black SOR).  Class 3 also holds the mixed loop's fused FP32
- * post-smoothing + FP64 defect pass.  `fine_only` selects the finest-level
- * bucket.
+ * weighting; in FP64 four sweeps of red-black SOR, and the cycle pass of
+ * large grids: a cycle's post-smoothing with the next one's pre-smoothing).
+ * Class 3 also holds the mixed loop's fused FP32 post-smoothing + FP64 defect
+ * pass.  `fine_only` selects the finest-level bucket.
  * lap_ctx_kernel_stats synchronises the stream. */
 lap_status lap_ctx_set_timing(lap_ctx* ctx, int32_t on);
 lap_status lap_ctx_kernel_stats(lap_ctx* ctx, int32_t kernel_class, int32_t fine_only,

@@ -15,10 +15,9 @@
 // Expression order and divisions follow the plain definition exactly (no
 // fused multiply-add: the file is built with -ffp-contract=off).
 //
-// Two solvers.  The segmented one (lines of up to 4095 unknowns along rows,
-// 1023 along columns) splits every line into short blocks solved in
-// parallel and couples them through a small reduced system (see
-// lap_kernels.hpp); it reads and writes every value once.  The sequential
+// Two solvers.  The segmented one (lines of up to 4095 unknowns) splits every
+// line into short blocks solved in parallel and couples them through a small
+// reduced system (see lap_kernels.hpp); it reads and writes every value once.  The sequential
 // one serves longer lines: columns, one thread per column line, marching j
 // (consecutive threads own consecutive lines, so every row access of a
 // wavefront is one contiguous span); rows, one 64-lane wavefront owns 64 row
@@ -261,7 +260,10 @@ void adi_seg_table_t(double Dd, double Ed, int K, T* tab) {
     // with a factor of at most amax^h, amax = max E_R / pivot_p; from the
     // distance on where amax^h / (1 - amax) is below 2^-60 (FP32: 2^-31) of
     // the line's largest value, a seventh bit below its rounding, further
-    // scan steps only add what rounding drops
+    // scan steps only add what rounding drops.  Against the line's largest
+    // value, that is: a value many orders below it keeps this error, not one
+    // of its own size, and a NaN or infinity on a line spreads as far as the
+    // reach in one solve, not over the whole line.
     R amax = 0;
     for (int p = 0; p < NR; ++p) amax = std::max(amax, std::fabs((R)tab[SEG_CQR + p]));
     const R drop = std::ldexp((R)1, sizeof(T) == 8 ? -60 : -31);

@@ -44,12 +44,11 @@ struct Tiling {
 // Halo of the canonical norm tiling: wide enough for a fused pass of two
 // sweeps and a residual + full weighting.
 constexpr int kNormH = 6;
-// Waves the canonical tiling of the stencil passes aims at.  On 8193^2 the
-// finest pre-smoothing pass took 259 us with 16384 waves (36-row chunks),
-// 252 us with 32768 (18 rows), 267 us with 49152 or 65536: halo rows shared
-// by neighbouring chunks come from L2, so shorter chunks pay little and
-// buy parallelism, up to a point.  Below ~6000 rows the 16-row minimum
-// decides instead.
+// Waves the canonical tiling of the residual kernel and, below kMergedNodes,
+// of the sweep passes with norms aims at.  Halo rows shared by neighbouring
+// chunks come from L2, so shorter chunks pay little and buy parallelism, up to
+// a point (8193^2: 18 rows; the residual kernel 96 us, on chunks of 300 rows
+// 114).  Below ~6000 rows the 16-row minimum decides instead.
 constexpr int kNormWaves = 32768;
 // Grids from kMergedNodes interior nodes on run one pass per cycle over the
 // finest level (merged_ok), whose norms, like those of every other sweep pass
@@ -115,23 +114,24 @@ enum NormKind { NORM_PASS = 0, NORM_DEFECT = 1, NORM_POSTDEF = 2, NORM_RES = 3 }
 // The defect pass keeps chunks of >= 64 rows on levels of more than 257
 // rows, >= 16 below.  Grids whose whole FP32 cycle fits one workgroup's LDS
 // (up to ~15k nodes) take this pass at every outer step; in a batch they
-// share a launch that the row walk of their chunks makes latency-bound
-// (64-row chunks: ~67 us per launch; 16-row chunks: 512-grid batch
-// 15.9 -> 15.4 ms).
+// share a launch that the row walk of their chunks makes latency-bound (a
+// solve of 48 ragged grids 2.18 ms with 16 rows, 2.38 with 64; of 512 grids
+// 9.08 and 9.28).
 constexpr int kDefectMinRows = 64;
 constexpr int kDefectShortRowsN = 257;
 // The post-smoothing + defect pass reads 2 * 2 + 1 halo rows above and below
-// each chunk: chunks of >= 64 rows up to 4097 rows (faster by 4% at 4097^2,
-// and by far in batches of small grids), of >= 16 rows beyond (the 16384
-// waves' chunks of 8193^2 are 36 rows; 64-row chunks were 1.5% slower).
+// each chunk: chunks of >= 64 rows up to 4097 rows (4% faster at 4097^2 when
+// the line was drawn; with the register ring 16 rows are 3% faster there,
+// 2.23 against 2.29 ms a solve, and even at 2049^2), of >= 16 rows beyond (the
+// 16384 waves' chunks of 8193^2 are 36 rows: 6.63 ms, with 64 rows 6.77).
 constexpr int kPostDefShortRowsN = 4097;
 // Levels of at most this many rows take the post-smoothing + defect pass's
 // norms per (window, block of 16 rows): one grid alone then walks 16-row
 // chunks (4x the waves of 64-row chunks: mixed solves of 129^2 / 257^2 /
-// 513^2 / 1025^2 grids 0.91 / 1.06 / 1.21 / 1.38 -> 0.62 / 0.73 / 0.85 /
-// 1.03 ms) while merged batch launches keep 64-row chunks (a 512-grid batch
-// with 16-row chunks: 15.4 -> 16.0 ms; with the block partials 15.6 ms),
-// and both reduce the same partials in the same order.
+// 513^2 / 1025^2 grids 0.53 / 0.61 / 0.71 / 0.85 -> 0.38 / 0.47 / 0.57 / 0.71
+// ms) while merged launches take 16 to 64 rows by their size (batch_rows; a
+// 512-grid batch 9.03 ms with 16 rows, 9.11 with 64), and all reduce the same
+// partials in the same order.
 constexpr int kRowPartN = 1025;
 constexpr int kRowBlock = 16;
 inline bool postdef_rowpart(int n) { return n <= kRowPartN; }

@@ -609,8 +609,10 @@ int subtree_root(const lap_grid* g, int lmin, int nu1) {
         // less than the level's two launches (257 x 129: 560 -> 528 us a solve); four, in
         // FP32 on 129 x 129, what its launches take and save two dispatches (1025^2: 882 ->
         // 860 us), but not at level 0, whose post-smoothing runs fused with the defect
-        // correction.  A V(0, nu) cycle in FP64 keeps the launches of a level of more than
-        // one patch a thread (3 us a cycle): the separate schedule it is checked against.
+        // correction (129 x 129 mixed: 906 us, as a subtree 1007).  A V(0, nu) cycle in FP64
+        // keeps the launches of a level of more than one patch a thread: they are its only
+        // fused passes, the schedule that its unfused one is checked against (the price: 1129
+        // against 1100 us a solve of 257 x 129 with nu = 2, 1253 against 1178 with nu = 4).
         const int most = l == 0 ? std::min(2, kSubPatches<T>) : sizeof(T) == 8 && nu1 == 0 ? 1 : kSubPatches<T>;
         if (sub_patches(G) > kSubBlock * most) continue;
         if (subtree_lds<T>(g->geo, l) <= (size_t)c->lds_max) return l;
@@ -3166,8 +3168,8 @@ int batch_kind(const Op& op) {
 // halo rows (up to 11 for a two-sweep pass, 21 for four sweeps) what a launch
 // that fills the device pays: the chunks are as long as leaves the launch
 // about kBatchWaves wavefronts, between 8 rows (the halo) and 32 (64 with four
-// sweeps).  512-grid ragged batch (54.6 M nodes): 32 rows (16:
-// 16.0 against 15.4 ms); 48 grids (4.9 M nodes): 10 rows, a solve 7.2 -> 6.8 ms.
+// sweeps).  Mixed solves of 512 ragged grids (54.6 M nodes, 32 rows): 9.13 ms, with
+// 16 rows 9.17, with 64 9.20; of 48 (12 rows): 2.20 ms, with 32 rows 2.45.
 constexpr int kBatchWaves = 4096;
 constexpr int kBatchRows[2] = {8, 32};
 constexpr int kBatchFourMaxRows = 64;
@@ -3285,9 +3287,8 @@ BatchItem make_item(lap_grid* g, const Op& op, const lap_opts& o, size_t nplan, 
     // minimise the latency of one grid's small level.  Inside a merged launch
     // over several grids plans of 4 or more grids use batch_rows, and every
     // plan of 2 or more grids 2 columns per lane (one launch per key; a
-    // 512-grid ragged batch of 33..1025 points a side: 13.8 ms with 4 columns
-    // per lane and >= 64 rows, 11.7 ms with 2 and >= 32; 15.4 ms with the
-    // table's chunks).
+    // 512-grid ragged batch of 33..1025 points a side: 9.4 ms with 4 columns
+    // per lane, 9.1 with 2, 13.5 with the table's chunks and widths).
     const bool tile_op = (op.kind == OP_SWEEP || op.kind == OP_RESTRICT) && !(op.flags & SW_NORM);
     if (tile_op && nplan >= kBatchManyGrids) {
         const int hi = (op.flags & SW_FOUR) ? kBatchFourMaxRows : kBatchRows[1];
