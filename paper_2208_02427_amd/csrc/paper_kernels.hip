@@ -389,7 +389,7 @@ __global__ __launch_bounds__(NT) void k_paper(PaperArgs A, int tables) {
         if constexpr (LINES) {
             // SLOR: rows j = 1..n-2; ADI: the rows, then columns i = 1..m-2
             const bool adi = A.method == LAP_ADI_LEX;
-            if (threadIdx.x < 64) {
+            if (NT == 64 || threadIdx.x < 64) {
                 for (int j = 1; j <= n - 2; ++j) {
                     double* const keep = adi ? u0 : nullptr;
                     mx = fmax(mx, tables ? paper_line<true, NT>(A, u, keep, j, 0, Fx, rhs, xq)
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(NT) void k_paper(PaperArgs A, int tables) {
                 paper_sync<NT>();
             }
         }
-        __syncthreads();
+        if constexpr (!LINES || NT > 64) __syncthreads();   // (a lone wavefront's lines end with one)
         ++it;
         q = paper_monitor(A, u, mx, r0, red);
         if (!isfinite(q) || q > 1e30) {
@@ -490,10 +490,13 @@ hipError_t launch_paper(const PaperArgs& a, int lds_max, hipStream_t s) {
             k_paper<64, true><<<1, 64, bytes, s>>>(a, tables ? 1 : 0);
         return hipGetLastError();
     }
-    // Jacobi: one to four nodes a thread, four wavefronts to a barrier, or sixteen wavefronts;
-    // SOR by diagonals: a wavefront, and a node a thread for a residual
-    int threads = a.method == LAP_JACOBI ? (N <= 1024 ? 256 : 1024) : 64;
-    if (residual) threads = std::min(kPaperLanes, (N + 63) / 64 * 64);
+    // Jacobi, and a residual after SOR by diagonals: one to four nodes a thread, four wavefronts to a
+    // barrier, or sixteen (33 x 33 to max|r|, 100 Jacobi iterations: 185 us with 256 threads, 223
+    // with 1024); the sum of a relative residual, whose lanes' order is given, a node a lane (the
+    // chamber, 100 iterations: 135 us with 384 threads, 182 with 256); SOR to its largest update: a
+    // wavefront
+    int threads = a.method == LAP_JACOBI || (residual && N > 64) ? (N <= 1024 ? 256 : 1024) : 64;
+    if (a.stop == LAP_STOP_REL_L2) threads = std::min(kPaperLanes, (N + 63) / 64 * 64);
     if (threads == 64)
         k_paper<64, false><<<1, 64, bytes, s>>>(a, 0);
     else
